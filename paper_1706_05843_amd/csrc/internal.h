@@ -122,6 +122,7 @@ struct HopArgs {
   double* partial;    // [nrhs][gridDim.x]
   int Vh, Ls, nrhs, rhs_block;
   int W;              // waves per work-group (1, 2 or 4)
+  int nt_out;         // 1: non-temporal output stores (set by the launcher)
   // optional CG step fused into a K3 (or D3) launch: work-group 0 of each RHS block
   // reduces fin_partial [nrhs][fin_nblk] (the previous launch's partial
   // sums) and applies finalize mode fin_mode to fin_S; null = none (other

@@ -1319,7 +1319,10 @@ hop_kernel(HopArgs a) {
       if constexpr (RT::OM == O_STORE && NRM16) {
         nrm = st_spinor16<false>(a.out, fd, r, s, EOFA_SITE, v);
       } else if constexpr (RT::OM == O_STORE) {
-        st_spinor<P>(a.out, fd, r, s, EOFA_SITE, v);
+        if (P != P16 && a.nt_out)
+          st_spinor_nt<P>(a.out, fd, r, s, EOFA_SITE, v);
+        else
+          st_spinor<P>(a.out, fd, r, s, EOFA_SITE, v);
       } else if constexpr (RT::OM == O_ADDZ) {
         cx<R> z[12];
         ld_spinor<P>(a.z, fd, r, s, EOFA_SITE, z);
@@ -1445,6 +1448,19 @@ size_t hop_lds_bytes(int prec, int role, int Ls, int W) {
                                                                   : hop_lds_p<P16>(role, Ls, W);
 }
 
+// Whether a launch writes its output with non-temporal stores: when input and
+// output together exceed the 256 MB MALL the next kernel finds nothing of the
+// output on the chip, and the store only evicts neighbour spinors this kernel
+// still gathers from L2. One right-hand side, one box: FP64 16^3 x 32 x 16
+// 169 -> 153 us, FP64 24^3 x 64 x 12 907 -> 862, FP32 411 -> 401. FP16S stays
+// with plain stores: level beyond the MALL, 5 % slower on the 16^3 x 32 x 16
+// solve, whose next kernel reads the output there. Several right-hand sides
+// gained nothing (12 x FP32: 5020 -> 5064 us).
+bool stream_output(int prec, const HopArgs& a) {
+  const size_t site = prec == P64 ? 192 : 96;
+  return prec != P16 && a.nrhs == 1 && 2 * site * a.Vh * a.Ls > (size_t(256) << 20);
+}
+
 template <int P, int ROLE>
 int launch_hop_t(const HopArgs& a, hipStream_t st, int* nblk_out) {
   const int Ls = a.Ls;
@@ -1456,6 +1472,7 @@ int launch_hop_t(const HopArgs& a, hipStream_t st, int* nblk_out) {
   HopArgs b = a;
   b.rhs_block = rb;
   b.W = W;
+  b.nt_out = stream_output(P, a) ? 1 : 0;
   void (*fn)(HopArgs) = hop_kernel<P, acc_prec<P>(), ROLE, 0>;
   if constexpr (P == P16)
     if (Ls % 4 == 0) fn = hop_kernel<P, acc_prec<P>(), ROLE, 4>;
