@@ -144,6 +144,7 @@ void run_layer(eofa_ctx* C, eofa_net* N, int l, bool adj, void* const* in, void*
   a.w = N->wb + 2 * N->woff[l];
   a.links = (const float*)C->links[P32][parity];
   a.nbr = C->nbr[parity];
+  a.order = C->order;
   a.Vh = C->g.Vh;
   a.Ls = C->g.Ls;
   a.Cin = adj ? N->ch[l + 1] : N->ch[l];

@@ -107,8 +107,9 @@ __device__ __forceinline__ cx<float> wload(const NetLayerArgs& a, int t, int c, 
 //  * otherwise mix first: z_c = sum_c' (W[2+e] + W[10+e] g_mu) X_c'(neighbour)
 //    for the CB outputs, then one link product per output: CB link products,
 //    but CB more spinors of registers.
-// The launcher takes TF when C_in <= CB. Registers: 48 CB (accumulators),
-// plus 48 CB for mix first.
+// Used for the smallest layers (see launch_pt_layer): TF for two to four
+// outputs, mix first for one. Registers: 48 CB (accumulators), plus 48 CB for
+// mix first.
 template <bool ADJ, int CB, bool TF>
 __global__ void __launch_bounds__(256) pt_layer_kernel(NetLayerArgs a) {
   __shared__ float2 s_w[NET_TERMS * 4 * NET_MAXC];  // [t][cc][ci], CB <= 4
@@ -207,6 +208,279 @@ __global__ void __launch_bounds__(256) pt_layer_kernel(NetLayerArgs a) {
   for (int cc = 0; cc < CB; ++cc) {
     if (cc >= nco) break;
     st_spinor<P32>(a.yout, fo, c0 + cc, s, i, acc[cc]);
+  }
+}
+
+// The layer on the matrix cores. A wave owns 16 consecutive 5D sites (columns
+// n = lane % 16) and its four lane groups g = lane / 16 take four transport
+// directions at once: in a pass, a lane loads and transports two input channels
+// of its column along its group's direction, and one K = 32 MFMA sums over the
+// four directions and two channels. With the spins paired by g_mu,
+// (g_mu v)_A = k_A v_B and (g_mu v)_B = k_B v_A, k a sign or +-i, the terms of
+// a direction on a pair (A, B) are
+//   y_A += Wa v_A + k_A Wb v_B,   y_B += k_B Wb v_A + Wa v_B,
+// real products of the weights (rows: Re, Im of each output channel; k folded
+// in) with (Re v_A, Im v_A, Re v_B, Im v_B) of the channels. A pass takes the
+// directions of mu = 0, 1 (pairs (0, 3), (1, 2)) or of mu = 2, 3 (pairs (0, 2),
+// (1, 3)), both signs, so that its pairs agree over the wave. A lane ends with
+// NCO output channels of its column; nothing moves between lanes by hand.
+// The weights are bfloat16 already; an FP32 activation is split exactly into
+// three bfloat16 numbers (8 + 8 + 8 bits, each the truncated rest of the one
+// before), so the products are those of the FP32 form, summed in FP32. Each pass
+// sums into zeros, smallest parts first, and joins the accumulator by a vector
+// add: added to a large accumulator inside the MFMA the sums round worse. The
+// error of a whole network against 64 bits, FP32 multiply-adds / MFMA into the
+// accumulator / as here: 1,8,8,8,1 at 16^3 x 32 x 16 3.7e-7 / 5.9e-7 / 2.5e-7,
+// 1,4,1 2.1e-7 / 2.8e-7 / 1.7e-7, 1,3,2,1 at 8^4 x 8 3.6e-7 / 2.8e-7 / 2.1e-7.
+// An infinite activation becomes NaN in the split.
+// What bounds it: vector instructions (5600 per wave and tile of 16 5D sites:
+// transports 288 and splits 264 of each pass), busy about two thirds of the
+// time, then the matrix cores (15 %). Taking two channels of all directions per
+// pass instead of one direction of all channels keeps the columns the XCD's
+// tiles gather at one time within its 4 MB L2 (with 8 channels at once 69 % of
+// the L2 requests missed, 6.4 GB a launch): 8 -> 8 channels, 16^3 x 32 x 16,
+// 1169 -> 985 us, with the outputs streamed past the MALL 948 us (and 2.5 % for
+// the accuracy of the sums); one thread per site, two outputs at a time, took
+// 4067 us.
+typedef __bf16 b8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned w4_t __attribute__((ext_vector_type(4)));
+
+constexpr int MF_MAXP = (NET_MAXC + 1) / 2;      // channel pairs
+constexpr int MF_FRAGS = MF_MAXP * 8 + 2;        // [pair of channels][mu class][spin pair][output], same-site upper, lower
+constexpr int MF_SITES = 9;                      // most 4D sites 16 consecutive 5D sites touch (Ls >= 2)
+constexpr int MF_LSTR = 73;                      // link stride in LDS
+
+__device__ __forceinline__ f32x4_t mf_mul(w4_t A, w4_t B, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8_t, A), __builtin_bit_cast(b8_t, B), c, 0, 0, 0);
+}
+
+// the three bfloat16 parts of a complex number as (Re, Im) words
+__device__ __forceinline__ void mf_split(cx<float> v, unsigned& hi, unsigned& mid, unsigned& lo) {
+  const unsigned r = __float_as_uint(v.r), i = __float_as_uint(v.i);
+  hi = __builtin_amdgcn_perm(i, r, 0x07060302u);
+  const float r1 = v.r - __uint_as_float(r & 0xFFFF0000u), i1 = v.i - __uint_as_float(i & 0xFFFF0000u);
+  const unsigned ur = __float_as_uint(r1), ui = __float_as_uint(i1);
+  mid = __builtin_amdgcn_perm(ui, ur, 0x07060302u);
+  const float r2 = r1 - __uint_as_float(ur & 0xFFFF0000u), i2 = i1 - __uint_as_float(ui & 0xFFFF0000u);
+  lo = __builtin_amdgcn_perm(__float_as_uint(i2), __float_as_uint(r2), 0x07060302u);
+}
+
+// direction of lane group g in a pass of mu class h
+__device__ __forceinline__ int mf_dir(int h, int g) { return 2 * h + (g & 1) + 4 * (g >> 1); }
+
+// weight W[t][co][ci] (conjugated and transposed in the adjoint) times i^rot,
+// as bfloat16 bits (Re, Im)
+template <bool ADJ>
+__device__ __forceinline__ uint2 mf_weight(const NetLayerArgs& a, int t, int rot, int co, int ci) {
+  const size_t k = ADJ ? (((size_t)t * a.Cin + ci) * a.Cout + co) * 2 : (((size_t)t * a.Cout + co) * a.Cin + ci) * 2;
+  unsigned r = a.w[k], i = a.w[k + 1];
+  if (ADJ) i ^= 0x8000u;
+  if (rot & 1) {  // i w = (-Im, Re)
+    const unsigned x = r;
+    r = i ^ 0x8000u;
+    i = x;
+  }
+  if (rot & 2) {
+    r ^= 0x8000u;
+    i ^= 0x8000u;
+  }
+  return make_uint2(r, i);
+}
+
+// lane (row, g)'s eight K values of fragment f: word h holds the row's factors
+// of (Re, Im) of operand word h (channel h / 2 of the pair, spin A or B by h % 2)
+template <bool ADJ, int NCO>
+__device__ __forceinline__ w4_t mf_fragment(const NetLayerArgs& a, int f, int row, int g) {
+  const int co = NCO == 2 ? row >> 1 : row >> 2, ri = NCO == 2 ? row & 1 : row & 3;
+  w4_t w;
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    const int part = h & 1;
+    int ci, t, rot = 0;
+    if (f >= MF_MAXP * 8) {  // same-site terms: group g holds channels 2g, 2g + 1
+      const int lower = f - MF_MAXP * 8;
+      ci = 2 * g + (h >> 1);
+      t = part ? 18 + lower : lower;
+    } else {
+      const int cls = (f >> 2) & 1, pair = (f >> 1) & 1, low = f & 1;
+      const int e = mf_dir(cls, g), mu = e & 3, te = ADJ ? (e ^ 4) : e;  // T_e^dag = T_{e^4}
+      ci = 2 * (f >> 3) + (h >> 1);
+      t = part == low ? 2 + te : 10 + te;
+      if (part != low) {  // k of (mu, pair, output): -i = i^3, -1 = i^2
+        if (mu == 0)
+          rot = low ? 1 : 3;
+        else if (mu == 1)
+          rot = pair ? 0 : 2;
+        else if (mu == 2)
+          rot = (low != pair) ? 1 : 3;
+      }
+    }
+    unsigned v = 0;
+    if (co < a.Cout && ci < a.Cin && ri < 2) {
+      const uint2 z = mf_weight<ADJ>(a, t, rot, co, ci);
+      v = ri == 0 ? (z.x | ((z.y ^ 0x8000u) << 16)) : (z.y | (z.x << 16));
+    }
+    w[h] = v;
+  }
+  return w;
+}
+
+struct MfIn {
+  cx<float> v[2][12];  // two channels
+};
+// channels c0, c0 + 1 at the 5D site of byte offset off within a plane; a
+// channel past the last reads the last one again (its weights are zero)
+__device__ __forceinline__ void mf_load(const float* base, const FD& f, int c0, unsigned off, MfIn& x) {
+#pragma unroll
+  for (int ch = 0; ch < 2; ++ch) {
+    const char* plane = (const char*)base + (size_t)min(c0 + ch, f.nrhs - 1) * 6 * qstride(f) * 16;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      const float4 v = *(const float4*)(plane + q * qstride(f) * 16 + off);
+      x.v[ch][2 * q] = {v.x, v.y};
+      x.v[ch][2 * q + 1] = {v.z, v.w};
+    }
+  }
+}
+
+// the split operand words of one spin pair and colour: (A, B) of both channels
+__device__ __forceinline__ void mf_operand(const cx<float>* va, const cx<float>* vb, w4_t* B) {
+#pragma unroll
+  for (int ch = 0; ch < 2; ++ch) {
+    unsigned h, m, l;
+    mf_split(va[ch], h, m, l);
+    B[0][2 * ch] = h;
+    B[1][2 * ch] = m;
+    B[2][2 * ch] = l;
+    mf_split(vb[ch], h, m, l);
+    B[0][2 * ch + 1] = h;
+    B[1][2 * ch + 1] = m;
+    B[2][2 * ch + 1] = l;
+  }
+}
+
+// one pass: transport the loaded channels along this lane's direction and
+// accumulate both outputs of each spin pair; LO: mu = 0, 1
+template <bool LO>
+__device__ __forceinline__ void mf_pass(const MfIn& x, const float2* L, const w4_t* frag, f32x4_t* acc) {
+  cx<float> U[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) U[k] = {L[k].x, L[k].y};
+#pragma unroll
+  for (int pair = 0; pair < 2; ++pair) {
+    const int sa = pair, sb = LO ? 3 - pair : 2 + pair;
+    const w4_t M1 = frag[(pair * 2) * 64], M2 = frag[(pair * 2 + 1) * 64];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      cx<float> va[2], vb[2];
+#pragma unroll
+      for (int ch = 0; ch < 2; ++ch) {
+        const cx<float>* p = x.v[ch] + sa * 3;
+        const cx<float>* q = x.v[ch] + sb * 3;
+        va[ch] = cfma(U[c * 3 + 2], p[2], cfma(U[c * 3 + 1], p[1], cmul(U[c * 3], p[0])));
+        vb[ch] = cfma(U[c * 3 + 2], q[2], cfma(U[c * 3 + 1], q[1], cmul(U[c * 3], q[0])));
+      }
+      w4_t B[3];
+      mf_operand(va, vb, B);
+      f32x4_t ya = {0.f, 0.f, 0.f, 0.f}, yb = ya;
+#pragma unroll
+      for (int k = 2; k >= 0; --k) {
+        ya = mf_mul(M1, B[k], ya);
+        yb = mf_mul(M2, B[k], yb);
+      }
+      acc[sa * 3 + c] += ya;
+      acc[sb * 3 + c] += yb;
+    }
+  }
+}
+
+template <bool ADJ, int NCO>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) pt_mfma_kernel(NetLayerArgs a, bool nt) {
+  extern __shared__ w4_t s_frag[];  // [npair * 8 + 2][64]
+  __shared__ float2 s_link[4 * MF_SITES * MF_LSTR];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 15, g = lane >> 4;
+  const int npair = (a.Cin + 1) / 2;
+  for (int j = tid; j < (npair * 8 + 2) * 64; j += 256) {
+    const int f = j >> 6;
+    s_frag[j] = mf_fragment<ADJ, NCO>(a, f < npair * 8 ? f : MF_MAXP * 8 + f - npair * 8, j & 15, (j >> 4) & 3);
+  }
+  __syncthreads();
+  const int n5 = a.Vh * a.Ls, Ls = a.Ls, p = a.parity;
+  const int ntile = (n5 + 63) / 64;
+  const FD fin = {Ls, a.Vh, a.Cin}, fo = {Ls, a.Vh, a.Cout};
+  const w4_t* frag = s_frag + lane;
+  const float* xo = a.xin[1 - p];
+  float2* wl = s_link + wave * MF_SITES * MF_LSTR;
+  const int e0 = mf_dir(0, g), e1 = mf_dir(1, g);
+  MfIn x0, x1;
+  // each XCD a contiguous run of tiles (work-groups are dealt round-robin; with
+  // fewer than 8 work-groups, each its own run)
+  const int nrun = min(8, (int)gridDim.x), run = blockIdx.x % nrun, nx = ((int)gridDim.x + nrun - 1 - run) / nrun;
+  const int t0 = (int)((size_t)ntile * run / nrun), t1 = (int)((size_t)ntile * (run + 1) / nrun);
+  for (int tile = t0 + (int)blockIdx.x / nrun; tile < t1; tile += nx) {
+    const int first = tile * 64 + wave * 16;
+    if (first >= n5) continue;  // uniform over the wave; no barrier below
+    const int idx = min(first + n, n5 - 1);
+    const bool live = first + n < n5;
+    const int k5 = idx / Ls, s = idx - k5 * Ls;
+    const int i = a.order[k5];
+    const int i0 = first / Ls, ns = min(first + 15, n5 - 1) / Ls - i0 + 1;
+    __builtin_amdgcn_wave_barrier();
+    for (int k = lane; k < ns * 72; k += 64) {
+      const int site = k / 72, r = k - site * 72;
+      wl[site * MF_LSTR + r] = ((const float2*)a.links)[(size_t)a.order[i0 + site] * 72 + r];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const float2* L = wl + (k5 - i0) * MF_LSTR;
+    const unsigned nb0 = (unsigned)(a.nbr[(size_t)i * 8 + e0] * Ls + s) * 16u;
+    const unsigned nb1 = (unsigned)(a.nbr[(size_t)i * 8 + e1] * Ls + s) * 16u;
+    f32x4_t acc[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) acc[k] = {0.f, 0.f, 0.f, 0.f};
+    // same-site terms, group g channels 2g and 2g + 1: operand (v, its s
+    // neighbour of the same chirality)
+    {
+      const int sm = s == 0 ? Ls - 1 : s - 1, sp = s == Ls - 1 ? 0 : s + 1;
+      const int c0 = min(2 * g, a.Cin - 1), c1 = min(2 * g + 1, a.Cin - 1);
+#pragma unroll
+      for (int ch = 0; ch < 2; ++ch) {
+        ld_spinor<P32>(a.xin[p], fin, ch ? c1 : c0, s, i, x0.v[ch]);
+        ld_half32(a.xin[p], fin, ch ? c1 : c0, ADJ ? sp : sm, i, 0, x1.v[ch]);
+        ld_half32(a.xin[p], fin, ch ? c1 : c0, ADJ ? sm : sp, i, 1, x1.v[ch]);
+      }
+      const w4_t fu = frag[npair * 8 * 64], fl = frag[(npair * 8 + 1) * 64];
+#pragma unroll
+      for (int k = 0; k < 12; ++k) {
+        const cx<float> va[2] = {x0.v[0][k], x0.v[1][k]}, vb[2] = {x1.v[0][k], x1.v[1][k]};
+        w4_t B[3];
+        mf_operand(va, vb, B);
+#pragma unroll
+        for (int q = 2; q >= 0; --q) acc[k] = mf_mul(k < 6 ? fu : fl, B[q], acc[k]);
+      }
+    }
+    // two channels at a time, both mu classes: the next pass's loads are in flight
+    mf_load(xo, fin, 0, nb0, x0);
+    for (int cp = 0; cp < npair; ++cp) {
+      mf_load(xo, fin, 2 * cp, nb1, x1);
+      mf_pass<true>(x0, L + e0 * 9, frag + cp * 8 * 64, acc);
+      if (cp + 1 < npair) mf_load(xo, fin, 2 * cp + 2, nb0, x0);
+      mf_pass<false>(x1, L + e1 * 9, frag + (cp * 8 + 4) * 64, acc);
+    }
+    if (live) {
+#pragma unroll
+      for (int ch = 0; ch < NCO; ++ch) {
+        if (NCO * g + ch >= a.Cout) break;
+        cx<float> y[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) y[k] = {acc[k][2 * ch], acc[k][2 * ch + 1]};
+        if (nt)
+          st_spinor_nt<P32>(a.yout, fo, NCO * g + ch, s, i, y);
+        else
+          st_spinor<P32>(a.yout, fo, NCO * g + ch, s, i, y);
+      }
+    }
   }
 }
 
@@ -701,18 +975,40 @@ void launch_pt_layer_cb(const NetLayerArgs& a, bool adj, hipStream_t st) {
     hipLaunchKernelGGL((pt_layer_kernel<false, CB, TF>), grid, dim3(256), 0, st, a);
 }
 
-// channel block and order by shape: one output channel mixes first (one
-// link product per direction); few inputs transport first; many inputs and
-// outputs mix first in blocks of 2
+template <int NCO>
+void launch_pt_mfma(const NetLayerArgs& a, bool adj, hipStream_t st) {
+  const int ntile = (a.Vh * a.Ls + 63) / 64;
+  const dim3 grid(std::min(ntile, 512));
+  const size_t lds = (size_t)((a.Cin + 1) / 2 * 8 + 2) * 64 * sizeof(w4_t);
+  const bool nt = (size_t)96 * a.Vh * a.Ls * (2 * a.Cin + a.Cout) > (size_t(256) << 20);
+  if (adj)
+    hipLaunchKernelGGL((pt_mfma_kernel<true, NCO>), grid, dim3(256), lds, st, a, nt);
+  else
+    hipLaunchKernelGGL((pt_mfma_kernel<false, NCO>), grid, dim3(256), lds, st, a, nt);
+}
+
+// Which kernel, measured on every channel pair at 16^3 x 32, Ls = 16 (us per
+// launch, one thread per site against the matrix cores): 1 -> 4 227 / 323,
+// 2 -> 2 277 / 341, 3 -> 1 402 / 455 stay; 1 -> 5 403 / 350, 2 -> 3 359 / 353,
+// 3 -> 2 505 / 474, 4 -> 1 538 / 469, 4 -> 4 659 / 532, 8 -> 4 2113 / 885,
+// 8 -> 8 4067 / 948 move; the same line holds at 8 x 12 x 6 x 16, Ls = 8
+// (4 -> 1 34 / 29, 8 -> 8 104 / 51, 1 -> 4 20 / 20).
+// One thread per site: one output channel mixes first (one link product per
+// direction), more outputs (of one or two inputs) transport first.
 void launch_pt_layer(const NetLayerArgs& a, bool adj, hipStream_t st) {
+  if (a.Cin >= 4 || a.Cin * a.Cout >= 5) {
+    if (a.Cout > 4)
+      launch_pt_mfma<2>(a, adj, st);
+    else
+      launch_pt_mfma<1>(a, adj, st);
+    return;
+  }
   if (a.Cout == 1)
     launch_pt_layer_cb<1, false>(a, adj, st);
-  else if (a.Cout == 2 && a.Cin <= 2)
+  else if (a.Cout == 2)
     launch_pt_layer_cb<2, true>(a, adj, st);
-  else if (a.Cin <= 4)
-    launch_pt_layer_cb<4, true>(a, adj, st);
   else
-    launch_pt_layer_cb<2, false>(a, adj, st);
+    launch_pt_layer_cb<4, true>(a, adj, st);
 }
 
 void launch_pt_wgrad(const NetGradArgs& a, int nblk, int accumulate, double* gw, hipStream_t st) {

@@ -16,6 +16,7 @@ struct NetLayerArgs {
   const unsigned short* w;   // bfloat16 (re, im) [20][Cout_fwd][Cin_fwd] of the forward layer
   const float* links;        // FP32 links of the output parity [Vh][8][9] complex
   const int* nbr;            // [Vh][8] neighbour index in the other parity
+  const int* order;          // [Vh] traversal position -> checkerboard index
   int Vh, Ls, Cin, Cout;     // of this (forward or adjoint) application
   int parity;
 };
