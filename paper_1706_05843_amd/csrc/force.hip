@@ -26,106 +26,173 @@ namespace eofa {
 
 namespace {
 
-__device__ __forceinline__ void coords_of(const int L[4], int parity, int i, int x[4]) {
-  const int hx = L[0] / 2;
-  int rest = i / hx;
-  const int xh = i - rest * hx;
-  x[1] = rest % L[1];
-  rest /= L[1];
-  x[2] = rest % L[2];
-  x[3] = rest / L[2];
-  x[0] = 2 * xh + ((parity + x[1] + x[2] + x[3]) & 1);
-}
-
 __device__ __forceinline__ size_t lex_of(const int L[4], const int x[4]) {
   return (((size_t)x[3] * L[2] + x[2]) * L[1] + x[1]) * L[0] + x[0];
 }
 
-// h = up + sg A lo for the 2 x 3 projected components of a 4 x 3 spinor
-// (A = -i sigma_1, -i sigma_2, -i sigma_3, 1 for mu = 0..3)
-__device__ __forceinline__ void project(const cx<double>* v, int mu, double sg, cx<double>* h) {
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const cx<double> u0 = v[c], u1 = v[3 + c], l0 = v[6 + c], l1 = v[9 + c];
-    if (mu == 0) {
-      h[c] = u0 - sg * mul_i(l1);
-      h[3 + c] = u1 - sg * mul_i(l0);
-    } else if (mu == 1) {
-      h[c] = u0 - sg * l1;
-      h[3 + c] = u1 + sg * l0;
-    } else if (mu == 2) {
-      h[c] = u0 - sg * mul_i(l0);
-      h[3 + c] = u1 + sg * mul_i(l1);
-    } else {
-      h[c] = u0 + sg * l0;
-      h[3 + c] = u1 + sg * l1;
-    }
-  }
-}
+// Bound by the loads of a and b: each site's spinors serve four links forward
+// and four backward. A work-group takes DV_T consecutive sites and all Ls; its
+// four waves take one direction each, a lane pair one link, a lane one of the
+// two projected components k (which needs spin k and its partner under g_mu
+// alone: half a spinor, half the 36 accumulators). Per s the tile's a and b and
+// those of the neighbours outside the tile go through LDS once, read by
+// neighbouring lanes (16 bytes each of a 192-byte spinor), while the previous s
+// is computed. 16^3 x 32 x 16: 378 us (2.5 TB/s of the compulsory bytes; with
+// the tiles in plain order 412), 24^3 x 32 x 12 898 us. One thread per site and
+// direction, reading its four spinors per s from memory 192 bytes a lane, took
+// 1256 and 3439 us.
+constexpr int DV_T = 32;                  // sites per work-group
+constexpr int DV_SLOTS = 5 * DV_T;        // the tile, then DV_T neighbours per direction
+constexpr int DV_ELEMS = DV_SLOTS * 12;   // complex numbers of one field staged per s
+constexpr int DV_ITER = (DV_ELEMS + 255) / 256;
 
-// 12 complex of field f at (s, lex); g5r5: read (gamma_5 R5 f)(s) = gamma_5 f(Ls-1-s)
-__device__ __forceinline__ void load12(const double2* f, int Ls, size_t V, int s, size_t lx, bool g5r5,
-                                       cx<double>* v) {
-  const int ss = g5r5 ? Ls - 1 - s : s;
-  const double2* p = f + ((size_t)ss * V + lx) * 12;
-#pragma unroll
-  for (int c = 0; c < 12; ++c) {
-    const double2 t = p[c];
-    const double sgn = (g5r5 && c >= 6) ? -1.0 : 1.0;
-    v[c] = {sgn * t.x, sgn * t.y};
-  }
-}
+__device__ __forceinline__ unsigned block_of(unsigned n) { return n % 4 == 0 ? 4 : (n % 2 == 0 ? 2 : 1); }
 
-// B += sum over the two projected components of h_v h_w^dag (3 x 3)
-__device__ __forceinline__ void outer_acc(const cx<double>* hv, const cx<double>* hw, cx<double>* B) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      cx<double> t = B[i * 3 + j];
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const cx<double> v = hv[c * 3 + i], w = hw[c * 3 + j];
-        t.r += v.r * w.r + v.i * w.i;  // v conj(w)
-        t.i += v.i * w.r - v.r * w.i;
-      }
-      B[i * 3 + j] = t;
-    }
-}
-
-__global__ void __launch_bounds__(128) dhop_deriv_kernel(DerivArgs d) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int mu = blockIdx.y, p = blockIdx.z;
-  if (i >= d.Vh) return;
-  int x[4], xp[4];
-  coords_of(d.L, p, i, x);
-  for (int k = 0; k < 4; ++k) xp[k] = x[k];
-  xp[mu] = (x[mu] + 1) % d.L[mu];
+__global__ void __launch_bounds__(256) dhop_deriv_kernel(DerivArgs d) {
+  extern __shared__ d2v_t s_f[];  // [2][DV_ELEMS]: a, then b
+  __shared__ unsigned s_site[DV_SLOTS];
+  __shared__ int s_nbr[4 * DV_T];   // slot of the site's neighbour x + mu
+  __shared__ int s_n[3];
   const size_t V = (size_t)d.L[0] * d.L[1] * d.L[2] * d.L[3];
-  const size_t lx = lex_of(d.L, x), lxp = lex_of(d.L, xp);
-  const double2* Up = d.links[p] + ((size_t)i * 8 + mu) * 9;
-  cx<double> U[9];
+  const int tid = threadIdx.x, mu = tid >> 6, lane = tid & 63, j = lane >> 1, k = lane & 1;
+  // a contiguous run of tiles per XCD (work-groups are dealt round-robin)
+  const int nblk = gridDim.x, xcd = blockIdx.x % 8;
+  unsigned tile = xcd * (nblk / 8) + min(xcd, nblk % 8) + blockIdx.x / 8;
+  // in blocks of up to 4 tiles of a plane x 4 z x 4 t, about the tiles an XCD has
+  // in flight, so that most z and t neighbours are fetched once per XCD
+  if (nblk >= 512 && d.L[0] * d.L[1] % DV_T == 0) {
+    const unsigned np = d.L[0] * d.L[1] / DV_T, bp = block_of(np), bz = block_of(d.L[2]), bt = block_of(d.L[3]);
+    const unsigned in = tile % (bp * bz * bt), blk = tile / (bp * bz * bt);
+    const unsigned nbp = np / bp, nbz = d.L[2] / bz;
+    const unsigned p = blk % nbp * bp + in % bp, z = blk / nbp % nbz * bz + in / bp % bz;
+    const unsigned t = blk / (nbp * nbz) * bt + in / (bp * bz);
+    tile = (t * d.L[2] + z) * np + p;
+  }
+  const unsigned base = tile * DV_T;
+  const unsigned nV = (unsigned)V;
+  // slots: the tile's sites, then the neighbours outside it, without gaps
+  {
+    unsigned ln = 0;
+    bool outside = false;
+    if (tid < 4 * DV_T) {
+      const int m = tid / DV_T, q = tid - m * DV_T;
+      const unsigned lx = min(base + q, nV - 1);
+      int x[4];
+      unsigned rest = lx;
+      for (int t = 0; t < 4; ++t) {
+        x[t] = rest % d.L[t];
+        rest /= d.L[t];
+      }
+      x[m] = x[m] + 1 == d.L[m] ? 0 : x[m] + 1;
+      ln = (unsigned)lex_of(d.L, x);
+      outside = ln < base || ln >= min(base + DV_T, nV);
+      if (m == 0) s_site[q] = lx;
+    }
+    const unsigned long long mask = __ballot(outside);
+    if (lane == 0 && mu < 2) s_n[mu] = __popcll(mask);
+    __syncthreads();
+    if (tid < 4 * DV_T) {
+      const int slot = DV_T + (mu ? s_n[0] : 0) + __popcll(mask & ((1ull << lane) - 1));
+      s_nbr[tid] = outside ? slot : (int)(ln - base);
+      if (outside) s_site[slot] = ln;
+    }
+    __syncthreads();
+  }
+  const int nelem = (DV_T + s_n[0] + s_n[1]) * 12;
+  // this thread's staged elements: offset within a field's s slice
+  unsigned off[DV_ITER];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) U[k] = {Up[k].x, Up[k].y};
+  for (int t = 0; t < DV_ITER; ++t) {
+    const int e = min(t * 256 + tid, nelem - 1), slot = e / 12, c = e - slot * 12;
+    off[t] = s_site[slot] * 12u + c;
+  }
+  d2v_t ra[DV_ITER], rb[DV_ITER];
+#pragma unroll
+  for (int t = 0; t < DV_ITER; ++t) ra[t] = rb[t] = d2v_t{0.0, 0.0};
+  auto fetch = [&](int s) {
+    const d2v_t* pa = (const d2v_t*)d.a + (size_t)(d.g5r5_a ? d.Ls - 1 - s : s) * V * 12;
+    const d2v_t* pb = (const d2v_t*)d.b + (size_t)s * V * 12;
+#pragma unroll
+    for (int t = 0; t < DV_ITER; ++t)
+      if (t * 256 < nelem) {  // uniform
+        ra[t] = pa[off[t]];
+        rb[t] = pb[off[t]];
+      }
+  };
+  const unsigned lx = base + j;
+  const bool live = lx < nV;
+  const int slot0 = j * 12, slot1 = s_nbr[mu * DV_T + j] * 12;
+  // A lo of component k: partner spin, whether times i, and its sign
+  // (A = -i sigma_1, -i sigma_2, -i sigma_3, 1)
+  const int part = (mu < 2 ? 3 - k : 2 + k) * 3, own = k * 3;
+  const bool times_i = mu == 0 || mu == 2;
+  const double sgn = mu == 0 ? -1.0 : mu == 3 ? 1.0 : k ? 1.0 : -1.0;
+  const double sgn_a = d.g5r5_a ? -sgn : sgn;  // gamma_5 on a's lower spins
   cx<double> B1[9], B2[9];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) B1[k] = B2[k] = {0.0, 0.0};
+  for (int q = 0; q < 9; ++q) B1[q] = B2[q] = {0.0, 0.0};
+  fetch(0);
   for (int s = 0; s < d.Ls; ++s) {
-    cx<double> v[12], w[12], hv[6], hw[6];
-    // B1: (1 - g_mu) b(x+mu) a(x)^dag
-    load12(d.b, d.Ls, V, s, lxp, false, v);
-    load12(d.a, d.Ls, V, s, lx, d.g5r5_a, w);
-    project(v, mu, -1.0, hv);
-    project(w, mu, -1.0, hw);
-    outer_acc(hv, hw, B1);
-    // B2: (1 + g_mu) b(x) a(x+mu)^dag
-    load12(d.b, d.Ls, V, s, lx, false, v);
-    load12(d.a, d.Ls, V, s, lxp, d.g5r5_a, w);
-    project(v, mu, 1.0, hv);
-    project(w, mu, 1.0, hw);
-    outer_acc(hv, hw, B2);
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < DV_ITER; ++t) {
+      const int e = t * 256 + tid;
+      if (e < nelem) {
+        s_f[e] = ra[t];
+        s_f[DV_ELEMS + e] = rb[t];
+      }
+    }
+    __syncthreads();
+    if (s + 1 < d.Ls) fetch(s + 1);
+    if (!live) continue;
+    // up + sg A lo of component k, three colours
+    auto project = [&](const d2v_t* v, double sg, cx<double>* h) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const d2v_t u = v[own + c], l = v[part + c];
+        const double zr = times_i ? -l.y : l.x, zi = times_i ? l.x : l.y;
+        h[c] = {fma(sg, zr, u.x), fma(sg, zi, u.y)};
+      }
+    };
+    auto outer = [](const cx<double>* v, const cx<double>* w, cx<double>* B) {
+#pragma unroll
+      for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {  // v conj(w)
+          cx<double>& t = B[r * 3 + c];
+          t.r = fma(v[r].r, w[c].r, fma(v[r].i, w[c].i, t.r));
+          t.i = fma(v[r].i, w[c].r, fma(-v[r].r, w[c].i, t.i));
+        }
+    };
+    cx<double> v[3], w[3];
+    project(s_f + DV_ELEMS + slot1, -sgn, v);  // B1: (1 - g_mu) b(x+mu) a(x)^dag
+    project(s_f + slot0, -sgn_a, w);
+    outer(v, w, B1);
+    project(s_f + DV_ELEMS + slot0, sgn, v);  // B2: (1 + g_mu) b(x) a(x+mu)^dag
+    project(s_f + slot1, sgn_a, w);
+    outer(v, w, B2);
   }
-  // y = coef (-1/2 U B1 + 1/2 B2 U^dag)
+  // the two components' sums (every lane takes part in the exchange)
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    B1[q].r += __shfl_xor(B1[q].r, 1, 64);
+    B1[q].i += __shfl_xor(B1[q].i, 1, 64);
+    B2[q].r += __shfl_xor(B2[q].r, 1, 64);
+    B2[q].i += __shfl_xor(B2[q].i, 1, 64);
+  }
+  if (!live) return;
+  int x[4];
+  unsigned rest = lx;
+  for (int t = 0; t < 4; ++t) {
+    x[t] = rest % d.L[t];
+    rest /= d.L[t];
+  }
+  const int p = (x[0] + x[1] + x[2] + x[3]) & 1;
+  const double2* Up = d.links[p] + ((size_t)(lx / 2) * 8 + mu) * 9;
+  cx<double> U[9];
+#pragma unroll
+  for (int q = 0; q < 9; ++q) U[q] = {Up[q].x, Up[q].y};
+  // y = coef (-1/2 U B1 + 1/2 B2 U^dag); lane k stores every second entry
   double2* out = d.y + ((size_t)mu * V + lx) * 9;
 #pragma unroll
   for (int r = 0; r < 3; ++r)
@@ -133,11 +200,12 @@ __global__ void __launch_bounds__(128) dhop_deriv_kernel(DerivArgs d) {
     for (int c = 0; c < 3; ++c) {
       cx<double> t1 = {0.0, 0.0}, t2 = {0.0, 0.0};
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        t1 = cfma(U[r * 3 + k], B1[k * 3 + c], t1);
-        const cx<double> ud = {U[c * 3 + k].r, -U[c * 3 + k].i};  // (U^dag)[k][c]
-        t2 = cfma(B2[r * 3 + k], ud, t2);
+      for (int q = 0; q < 3; ++q) {
+        t1 = cfma(U[r * 3 + q], B1[q * 3 + c], t1);
+        const cx<double> ud = {U[c * 3 + q].r, -U[c * 3 + q].i};  // (U^dag)[q][c]
+        t2 = cfma(B2[r * 3 + q], ud, t2);
       }
+      if (((r * 3 + c) & 1) != k) continue;
       const cx<double> yv = {d.coef * 0.5 * (t2.r - t1.r), d.coef * 0.5 * (t2.i - t1.i)};
       double2 o = d.accumulate ? out[r * 3 + c] : make_double2(0.0, 0.0);
       o.x += yv.r;
@@ -216,8 +284,8 @@ void launch_fold_force(int Lx, size_t rows, const void* F2, void* F, hipStream_t
 }
 
 void launch_dhop_deriv(const DerivArgs& d, hipStream_t st) {
-  dim3 grid((d.Vh + 127) / 128, 4, 2);
-  hipLaunchKernelGGL(dhop_deriv_kernel, grid, dim3(128), 0, st, d);
+  const int ntile = (2 * d.Vh + DV_T - 1) / DV_T;
+  hipLaunchKernelGGL(dhop_deriv_kernel, dim3(ntile), dim3(256), 2 * DV_ELEMS * sizeof(double2), st, d);
 }
 
 void launch_force_project(size_t nlinks, void* y, hipStream_t st) {
