@@ -795,7 +795,7 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
   CHK(ws(C, "wS", bS, &wS));
   CHK(ws(C, "rin", bS, &rin));
   CHK(ws(C, "xin", bX, &xin));
-  const int maxblk = std::max(hop_blocks(P64, g.Vh, g.Ls, 1), (g.Ls * g.Vh + 255) / 256);  // W = 1 has the most blocks
+  const int maxblk = std::max(hop_blocks(P64, g.Vh, g.Ls, 1, 1), (g.Ls * g.Vh + 255) / 256);  // W = 1 has the most blocks
   CHK(ws(C, "partial", sizeof(double) * (size_t)maxblk * nrhs, &partial_v));
   double* partial = (double*)partial_v;
   CgState Sst;
@@ -1021,7 +1021,7 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
         x->rhs_block = rb;
       }
     }
-    const int nbh = hop_blocks(S, g.Vh, g.Ls, k1.W);
+    const int nbh = hop_blocks(S, g.Vh, g.Ls, k1.W, nrhs);
 
     int it = 0;
     const int cap = fixed ? prm->fixed_iters : prm->max_iter + 1;
@@ -1183,7 +1183,7 @@ int eofa::normal_op_fp32(eofa_ctx* C, const eofa_system* sys, const void* in, vo
   void *te, *w, *pv;
   CHK(ws(C, "na_te", b32, &te));
   CHK(ws(C, "na_w", b32, &w));
-  const int maxblk = std::max(hop_blocks(P32, g.Vh, g.Ls, 1), (g.Ls * g.Vh + 255) / 256);
+  const int maxblk = std::max(hop_blocks(P32, g.Vh, g.Ls, 1, 1), (g.Ls * g.Vh + 255) / 256);
   CHK(ws(C, "na_partial", sizeof(double) * (size_t)maxblk, &pv));
   HopArgs k1 = base_args(C, P32, 0, 1);
   k1.in = in;
@@ -1270,7 +1270,7 @@ struct Fgcg {
     for (int k = 0; k < 12; ++k) CHK(ws(C, names[k], b64, bufs[k]));
     CHK(ws(C, "fg_r32", b32, &r32));
     CHK(ws(C, "fg_z32", b32, &z32));
-    const int maxblk = std::max({hop_blocks(P64, g.Vh, g.Ls, 1), (g.Ls * g.Vh + 255) / 256, 512 * FG_CHUNK});
+    const int maxblk = std::max({hop_blocks(P64, g.Vh, g.Ls, 1, 1), (g.Ls * g.Vh + 255) / 256, 512 * FG_CHUNK});
     void* pv;
     CHK(ws(C, "fg_partial", sizeof(double) * 2 * (size_t)maxblk, &pv));
     partial = (double*)pv;
@@ -1633,7 +1633,7 @@ extern "C" int eofa_cg_solve_noalloc(eofa_ctx* C, const eofa_system* sys, const 
   const Geometry& g = C->g;
   const int S = prm->inner_prec, PX = S == P64 ? P64 : P32;
   const size_t b64 = packed_bytes(P64, g, nrhs), bS = packed_bytes(S, g, nrhs), bX = packed_bytes(PX, g, nrhs);
-  const size_t maxblk = std::max(hop_blocks(P64, g.Vh, g.Ls, 1), (g.Ls * g.Vh + 255) / 256);
+  const size_t maxblk = std::max(hop_blocks(P64, g.Vh, g.Ls, 1, 1), (g.Ls * g.Vh + 255) / 256);
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   const size_t need = 7 * al(b64) + 5 * al(bS) + al(bX) + al(sizeof(double) * maxblk * nrhs) +
                       al((8 * sizeof(double) + 5 * sizeof(int)) * nrhs + 64) +
@@ -1728,7 +1728,7 @@ int forecast(eofa_ctx* C, const eofa_system* sys, const void* rhs, const std::ve
   CHK(ws(C, "fc_mo", b64, &mo));
   CHK(ws(C, "fc_zero", b64, &zero));
   CHK(ws(C, "fc_g5", 2 * b64 * (size_t)N, &g5));
-  const int maxblk = std::max({hop_blocks(P64, g.Vh, g.Ls, 1), (g.Ls * g.Vh + 255) / 256, 2048});
+  const int maxblk = std::max({hop_blocks(P64, g.Vh, g.Ls, 1, 1), (g.Ls * g.Vh + 255) / 256, 2048});
   CHK(ws(C, "fc_partial", sizeof(double) * 2 * (size_t)maxblk, &pv));
   CHK(ws(C, "fc_dot", sizeof(double) * (4 * (size_t)N * N + 2 * (size_t)N), &dv));
   CHK(stage(C, sizeof(double) * (4 * (size_t)N * N + 2 * (size_t)N)));

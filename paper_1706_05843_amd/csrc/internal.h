@@ -134,7 +134,11 @@ struct HopArgs {
 
 // kernel launchers (kernels.hip)
 int launch_hop(int prec, int role, const HopArgs& a, hipStream_t st, int* nblk_out);
-int hop_blocks(int prec, int Vh, int Ls, int W);
+// the same for launches that hop_is_small takes (hop_small.hip)
+int launch_hop_small(int prec, int role, const HopArgs& a, hipStream_t st);
+bool hop_is_small(int prec, int Vh, int Ls, int nrhs);
+// work-groups of a launch per right-hand side (one partial sum each)
+int hop_blocks(int prec, int Vh, int Ls, int W, int nrhs);
 // default waves per work-group for Ls (at most 20 4D sites per work-group)
 int default_waves(int Ls);
 // LDS bytes the hop kernel of this role needs, for the precision and shape

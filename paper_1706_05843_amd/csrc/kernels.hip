@@ -22,62 +22,13 @@
 #include <cstdio>
 
 #include "device_common.h"
+#include "hop_common.h"
 #include "internal.h"
 
 namespace eofa {
 
 // ---------------------------------------------------------------------------
 // the fused hop kernel
-
-// epilogue applied to the hop result h = Dhop (D~ in) of each 5D site:
-//   A_ID    v = h              A_NEG  v = -h
-//   A_MAT   v = M h            (dense Ls x Ls per chirality, through LDS)
-//   A_DTT   v = D~^T h         A_NDTT v = -D~^T h   (structured: lane exchange)
-//   A_MATDT v = M D~^T h
-//   A_DMINV v = D~ M_ee^-1 h   A_MINVDT v = M_ee^-T D~^T h   (the inverse
-//           structured along the column: minv_rows for Ls = 16, minv_cols
-//           otherwise; D~ and D~^T by lane exchange)
-// plus the same-site term B y:
-//   B_MEE   + M_ee y           B_MEET + M_ee^T y    (structured: lane exchange)
-//   B_MEE_DTI + M_ee D~^-1 y   (y = p~ = D~ p; D~^-1 a geometric series along s)
-enum { A_ID = 0, A_NEG = 1, A_MAT = 2, A_DTT = 3, A_NDTT = 4, A_MATDT = 5, A_DMINV = 6, A_MINVDT = 7 };
-enum { B_NONE = 0, B_MEE = 1, B_MEET = 2, B_DENSE = 3, B_MEE_DTI = 4 };
-enum { O_STORE = 0, O_ADDZ = 1, O_RUPD = 2, O_STORE_R = 3 };
-
-template <int ROLE>
-struct RoleT;
-#define EOFA_ROLE(NAME, dag, pre, am, bm, om, nrm)   \
-  template <>                                        \
-  struct RoleT<NAME> {                               \
-    static constexpr bool DAG = dag, PRE = pre;      \
-    static constexpr int AM = am;                    \
-    static constexpr int BM = bm;                    \
-    static constexpr int OM = om;                    \
-    static constexpr bool NRM = nrm;                 \
-  };
-EOFA_ROLE(ROLE_DSLASH, false, true, A_ID, B_NONE, O_STORE, false)
-EOFA_ROLE(ROLE_DSLASH_DAG, true, false, A_DTT, B_NONE, O_STORE, false)
-EOFA_ROLE(ROLE_K1, false, true, A_DMINV, B_NONE, O_STORE, false)
-EOFA_ROLE(ROLE_K2, false, false, A_NEG, B_MEE, O_STORE, true)
-EOFA_ROLE(ROLE_K3, true, false, A_MINVDT, B_NONE, O_STORE, false)
-EOFA_ROLE(ROLE_K4, true, false, A_NDTT, B_MEET, O_RUPD, true)
-EOFA_ROLE(ROLE_K4S, true, false, A_NDTT, B_MEET, O_STORE_R, true)
-EOFA_ROLE(ROLE_SRC, false, true, A_ID, B_NONE, O_ADDZ, false)
-EOFA_ROLE(ROLE_RES, false, false, A_NEG, B_MEE, O_ADDZ, true)
-EOFA_ROLE(ROLE_FULLRES, false, true, A_ID, B_MEE, O_ADDZ, true)
-// dense (non-Cayley) form: off-parity blocks Dhop alone, same-parity blocks dense
-EOFA_ROLE(ROLE_D1, false, false, A_MAT, B_NONE, O_STORE, false)
-EOFA_ROLE(ROLE_D2, false, false, A_NEG, B_DENSE, O_STORE, true)
-EOFA_ROLE(ROLE_D3, true, false, A_MAT, B_NONE, O_STORE, false)
-EOFA_ROLE(ROLE_D4, true, false, A_NEG, B_DENSE, O_RUPD, true)
-EOFA_ROLE(ROLE_D4S, true, false, A_NEG, B_DENSE, O_STORE_R, true)
-EOFA_ROLE(ROLE_DSRC, false, false, A_ID, B_NONE, O_ADDZ, false)
-EOFA_ROLE(ROLE_DRES, false, false, A_NEG, B_DENSE, O_ADDZ, true)
-EOFA_ROLE(ROLE_DFULLRES, false, false, A_ID, B_DENSE, O_ADDZ, true)
-// the search direction held as p~ = D~ p: no premix in K1, D~^-1 on the same-site term of K2
-EOFA_ROLE(ROLE_K1T, false, false, A_DMINV, B_NONE, O_STORE, false)
-EOFA_ROLE(ROLE_K2T, false, false, A_NEG, B_MEE_DTI, O_STORE, true)
-#undef EOFA_ROLE
 
 constexpr int LSTR = 73;  // padded link stride per site in LDS (complex units)
 constexpr int NSTR = 9;   // padded neighbour stride per site in LDS
@@ -761,15 +712,6 @@ __device__ __forceinline__ void series_rows(cx<R>* z, int s, R x1, R x2, R x4, R
 // with a_s from the host. A^-T uses L^T, which for L_+ is L_- in structure
 // and vice versa. TRANS selects M_ee^-T. About 250 VALU operations per lane
 // instead of the 768 of the dense Ls x Ls product.
-// 1/x: the hardware reciprocal (1 ulp) in FP32, a division in FP64
-template <class R>
-__device__ __forceinline__ R recip(R x) {
-  if constexpr (sizeof(R) == 4)
-    return __builtin_amdgcn_rcpf(x);
-  else
-    return R(1) / x;
-}
-
 template <class R, bool TRANS, bool NORM = true>
 __device__ __forceinline__ void minv_rows(cx<R>* v, int s, int g, R bee, R cee, R m, R sk, int chi, R a_s) {
   const R rho = cee * recip(bee);
@@ -875,27 +817,6 @@ __device__ __forceinline__ void dtinv(cx<R>* v, int s, int g, int Ls, R cpd, R c
       for (int c = 0; c < 6; ++c) z[c] = scale * z[c];
     }
   }
-}
-
-// the normalisations the structured inverses leave to their callers:
-// 1/(bee (1 + m rho^Ls)), rho = cee/bee, of M_ee^-1 (unshifted part), and
-// 1/((c+d)(1 + m q^Ls)), q = (c-d)/(c+d), of D~^-1
-template <class R>
-__device__ __forceinline__ R power_ls(R x, int Ls) {  // x^Ls by squaring
-  R p = R(1), b = x;
-  for (int e = Ls; e > 0; e >>= 1) {
-    if (e & 1) p *= b;
-    b *= b;
-  }
-  return p;
-}
-template <class R>
-__device__ __forceinline__ R minv_norm(R bee, R cee, R m, int Ls) {
-  return recip(bee * (R(1) + m * power_ls(cee * recip(bee), Ls)));
-}
-template <class R>
-__device__ __forceinline__ R dtinv_norm(R cpd, R cmd, R m, int Ls) {
-  return recip(cpd * (R(1) + m * power_ls(cmd * recip(cpd), Ls)));
 }
 
 // The same structured inverse for any Ls, by lane permutes within the
@@ -1022,43 +943,6 @@ __device__ __forceinline__ void load_y(const void* y, const FD& fd, int r, int s
   } else {
     ld_spinor<P>(y, fd, r, s, site, out);
   }
-}
-
-__device__ void finalize_step(int mode, double sum, const CgState& S, int r, double* out);
-
-// A CG step fused into a hop launch (work-group 0 of each right-hand-side
-// block): the previous launch's nblk partial sums of right-hand side r,
-// reduced by the whole work-group in a fixed order (8 independent sums per
-// thread, then lanes, then waves), then finalize_step on thread 0. red: one
-// double per wave.
-__device__ __forceinline__ void fin_block(int mode, const double* __restrict__ pr, int nblk, const CgState& S, int r,
-                                          double* red) {
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  double acc[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) acc[k] = 0.0;
-  for (int j0 = tid; j0 < nblk; j0 += 8 * nthr) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int j = j0 + k * nthr;
-      if (j < nblk) acc[k] += pr[j];
-    }
-  }
-#pragma unroll
-  for (int w = 4; w > 0; w >>= 1)
-#pragma unroll
-    for (int k = 0; k < w; ++k) acc[k] += acc[k + w];
-  double t = acc[0];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
-  if ((tid & 63) == 0) red[tid >> 6] = t;
-  __syncthreads();
-  if (tid == 0) {
-    double sum = 0.0;
-    for (int w = 0; w < (nthr + 63) / 64; ++w) sum += red[w];
-    finalize_step(mode, sum, S, r, nullptr);
-  }
-  __syncthreads();
 }
 
 // RL = 16: Ls = 16, each site's s-column is one DPP row and every exchange
@@ -1392,8 +1276,21 @@ constexpr int acc_prec() {
   return P;
 }
 
-int hop_blocks(int prec, int Vh, int Ls, int W) {
-  (void)prec;
+// Launches whose tiles of one wave leave most of the chip idle go to the kernel
+// of hop_small.hip, which shares each tile among eight waves. Time per FP64 /
+// FP32 CG iteration there and here (us): 16 tiles (4^4, Ls = 8) 34 and 57 / 31
+// and 47; 256 (8^4) 40 and 65 / 33 and 52; 512 53 and 74 / 38 and 57; 820 (Ls =
+// 12) 86 and 89 / 54 and 64; 1024 91 and 98 / 54 and 70; 2048 167 and 144 / 86
+// and 88, at Ls = 16, whose row form here is faster, 180 and 129 / 93 and 71.
+// The single hop in FP64 is level at 820.
+bool hop_is_small(int prec, int Vh, int Ls, int nrhs) {
+  if (prec == P16) return false;
+  const size_t G = sites_per_wave(Ls), tiles = ((size_t)Vh + G - 1) / G;
+  return tiles * nrhs <= (prec == P64 ? 640u : 1024u) / (Ls == 16 ? 2 : 1);
+}
+
+int hop_blocks(int prec, int Vh, int Ls, int W, int nrhs) {
+  if (hop_is_small(prec, Vh, Ls, nrhs)) W = 1;
   const int SBk = W * sites_per_wave(Ls);
   return (Vh + SBk - 1) / SBk;
 }
@@ -1467,7 +1364,7 @@ int launch_hop_t(const HopArgs& a, hipStream_t st, int* nblk_out) {
   const int Ls = a.Ls;
   const int W = a.W >= 1 && a.W <= MAXW ? a.W : default_waves(Ls);
   const size_t lds = hop_lds_t<P, ROLE>(Ls, W);
-  const int nblk = hop_blocks(P, a.Vh, Ls, W);
+  const int nblk = hop_blocks(P, a.Vh, Ls, W, a.nrhs);
   const int rb = a.rhs_block > 0 ? a.rhs_block : 1;
   dim3 grid(nblk, (a.nrhs + rb - 1) / rb);
   HopArgs b = a;
@@ -1516,6 +1413,10 @@ int launch_hop_p(int role, const HopArgs& a, hipStream_t st, int* nb) {
 }
 
 int launch_hop(int prec, int role, const HopArgs& a, hipStream_t st, int* nblk_out) {
+  if (hop_is_small(prec, a.Vh, a.Ls, a.nrhs)) {
+    if (nblk_out) *nblk_out = hop_blocks(prec, a.Vh, a.Ls, 1, a.nrhs);
+    return launch_hop_small(prec, role, a, st);
+  }
   switch (prec) {
     case P64: return launch_hop_p<P64>(role, a, st, nblk_out);
     case P32: return launch_hop_p<P32>(role, a, st, nblk_out);
@@ -2220,60 +2121,6 @@ void launch_cg_update(int ps, const Geometry& g, void* x, const void* r, void* p
 
 // ---------------------------------------------------------------------------
 // CG scalar finalisation: one block per right-hand side, fixed summation order
-
-// one CG scalar step for right-hand side r from the reduced sum
-__device__ void finalize_step(int mode, double sum, const CgState& S, int r, double* out) {
-  if (mode == FIN_NORM) {
-    out[r] = sum;
-    return;
-  }
-  if (mode == FIN_INIT) {
-    S.rr[r] = sum;
-    S.stop[r] = S.tol2[r] * sum;
-    S.guard[r] *= sum;
-    S.iter[r] = 0;
-    S.u2run[r] = 0;
-    S.breakdown[r] = 0;
-    S.halt[r] = (sum == 0.0 || S.max_iter[r] <= 0) ? 1 : 0;
-    if (!isfinite(sum)) {
-      S.breakdown[r] = 1;
-      S.halt[r] = 1;
-    }
-    return;
-  }
-  if (mode == FIN_ALPHA) {
-    if (S.halt[r]) return;
-    S.ww[r] = sum;
-    if (!(sum > 0.0) || !isfinite(sum)) {
-      S.breakdown[r] = 1;
-      S.halt[r] = 1;
-      S.alpha[r] = 0.0;
-      return;
-    }
-    S.alpha[r] = S.rr[r] / sum;
-    return;
-  }
-  // FIN_BETA
-  if (S.halt[r]) {
-    S.u2run[r] = 0;
-    return;
-  }
-  const double rrn = sum;
-  S.beta[r] = rrn / S.rr[r];
-  S.rr[r] = rrn;
-  S.iter[r] += 1;
-  S.u2run[r] = 1;
-  if (!isfinite(rrn)) {
-    S.breakdown[r] = 1;
-    S.halt[r] = 1;
-    S.u2run[r] = 0;
-  } else if (rrn <= S.stop[r] || S.iter[r] >= S.max_iter[r]) {
-    S.halt[r] = 1;
-  } else if (S.guard[r] > 0.0 && rrn > S.guard[r]) {
-    S.halt[r] = 1;
-    S.breakdown[r] = 2;
-  }
-}
 
 constexpr int FIN_THREADS = 1024, FIN_LOADS = 16;
 
