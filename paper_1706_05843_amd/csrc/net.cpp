@@ -162,6 +162,7 @@ void run_wgrad(eofa_ctx* C, eofa_net* N, int l, void* const* x, void* const* g, 
     ga.links[p] = (const float*)C->links[P32][p];
     ga.nbr[p] = C->nbr[p];
   }
+  ga.order = C->order;
   ga.partial = N->partial;
   ga.Vh = C->g.Vh;
   ga.Ls = C->g.Ls;

@@ -485,130 +485,141 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))
 }
 
 // dL/dW*[t][c][ci] partial sums: sum over sites of G_c(x) . conj((S_t X_ci)(x)).
-// Work-group (blk, grp * ncb + cb, parity) computes two terms of group grp:
-// grp < 8 the transport e = grp (terms 2+e and 10+e), grp = 8 the same-site
-// chirality terms (0, 1), grp = 9 the s shifts (18, 19); output channels
-// cb*WG_CB .. +WG_CB-1, all input channels. Each thread loads its site's G_c
-// once and each transported input once per channel block.
-constexpr int WG_CB = 2;
-constexpr int WG_GROUPS = 10;
+// A work-group takes a block of CB output and CI input channels (CB CI <= 4),
+// one parity and one of two sets of terms: set 0 the transports of mu = 0, 1 with
+// the same-site terms, set 1 those of mu = 2, 3 with the s shifts. A thread loads its
+// site's G_c once for all terms of the set and each transported input once for
+// all its output channels: the loads (G, then the gathers) bound it, 1.5 KB a
+// site for 1 -> 4 channels, where a work-group per term pair and two output
+// channels read 5.8 KB. Sites run in the traversal order, a contiguous eighth
+// per XCD, so that neighbours meet in its L2. 16^3 x 32, Ls = 16: 1 -> 4 channels
+// 489 us a launch, 4 -> 1 783, both 1651 before. (Transporting G instead of X
+// where there are fewer outputs saves a third of the multiplications of 4 -> 1
+// and took 863.)
+constexpr int WG_TERMS = 10;  // terms of a set
 
-__global__ void __launch_bounds__(256) pt_wgrad_kernel(NetGradArgs a) {
-  const int ncb = (a.Cout + WG_CB - 1) / WG_CB;
-  const int grp = blockIdx.y / ncb, cb = blockIdx.y - grp * ncb;
-  const int c0 = cb * WG_CB;
-  const int nco = min(WG_CB, a.Cout - c0);
-  const int p = blockIdx.z;
+__device__ __forceinline__ void wg_acc(const cx<float>* g, const cx<float>* v, float* acc, int q0, int q1) {
+  float sr = 0.f, si = 0.f;
+#pragma unroll
+  for (int q = 0; q < 12; ++q) {  // g conj(v)
+    if (q < q0 || q >= q1) continue;
+    sr = fmaf(g[q].r, v[q].r, fmaf(g[q].i, v[q].i, sr));
+    si = fmaf(g[q].i, v[q].r, fmaf(-g[q].r, v[q].i, si));
+  }
+  acc[0] += sr;
+  acc[1] += si;
+}
+
+template <int CB, int CI, int SET>
+__device__ __forceinline__ void wgrad_set(const NetGradArgs& a, int c0, int ci0, int p, double* dred) {
+  constexpr int NT = WG_TERMS;
   const FD fx = {a.Ls, a.Vh, a.Cin}, fg = {a.Ls, a.Vh, a.Cout};
-  // [cc][ci][term a / b]
-  float ar[WG_CB][NET_MAXC][2], ai[WG_CB][NET_MAXC][2];
+  float acc[CB][CI][NT][2];
 #pragma unroll
-  for (int cc = 0; cc < WG_CB; ++cc)
+  for (int cc = 0; cc < CB; ++cc)
 #pragma unroll
-    for (int ci = 0; ci < NET_MAXC; ++ci)
+    for (int k = 0; k < CI; ++k)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) ar[cc][ci][h] = ai[cc][ci][h] = 0.f;
-  const int n = a.Vh * a.Ls;
-  for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += gridDim.x * blockDim.x) {
-    const int i = idx / a.Ls, s = idx - i * a.Ls;
-    cx<float> g[WG_CB][12];
+      for (int t = 0; t < NT; ++t) acc[cc][k][t][0] = acc[cc][k][t][1] = 0.f;
+  const int n = a.Vh * a.Ls, nblk = gridDim.x;
+  // a contiguous eighth of the sites per XCD (work-groups are dealt round-robin)
+  const int nrun = min(8, nblk), run = blockIdx.x % nrun, nx = (nblk + nrun - 1 - run) / nrun;
+  const int lo = (int)((size_t)n * run / nrun), hi = (int)((size_t)n * (run + 1) / nrun);
+  for (int idx = lo + (blockIdx.x / nrun) * 256 + threadIdx.x; idx < hi; idx += nx * 256) {
+    const int k5 = idx / a.Ls, s = idx - k5 * a.Ls, i = a.order[k5];
+    cx<float> g[CB][12];
 #pragma unroll
-    for (int cc = 0; cc < WG_CB; ++cc) {
-      if (cc >= nco) break;
-      ld_spinor<P32>(a.g[p], fg, c0 + cc, s, i, g[cc]);
-    }
+    for (int cc = 0; cc < CB; ++cc) ld_spinor<P32>(a.g[p], fg, min(c0 + cc, a.Cout - 1), s, i, g[cc]);
 #pragma unroll
-    for (int ci = 0; ci < NET_MAXC; ++ci) {
-      if (ci >= a.Cin) break;
-      // va = S_ta X_ci, vb = S_tb X_ci at (x, s)
-      cx<float> va[12], vb[12];
-      if (grp < 8) {
-        const int j = a.nbr[p][(size_t)i * 8 + grp];
-        ld_spinor<P32>(a.x[1 - p], fx, ci, s, j, va);
-        link_mul((const float2*)a.links[p] + ((size_t)i * 8 + grp) * 9, va);
-        gamma_mul(grp & 3, va, vb);
-      } else if (grp == 8) {
-        ld_spinor<P32>(a.x[p], fx, ci, s, i, va);
+    for (int d = 0; d < 4; ++d) {
+      const int mu = 2 * SET + (d & 1), e = mu + 4 * (d >> 1);
+      const int j = a.nbr[p][(size_t)i * 8 + e];
+      const float2* L = (const float2*)a.links[p] + ((size_t)i * 8 + e) * 9;
 #pragma unroll
-        for (int q = 0; q < 12; ++q) vb[q] = va[q];
+      for (int k = 0; k < CI; ++k) {
+        cx<float> v[12], gv[12];
+        ld_spinor<P32>(a.x[1 - p], fx, min(ci0 + k, a.Cin - 1), s, j, v);
+        link_mul(L, v);
+        gamma_mul(mu, v, gv);
 #pragma unroll
-        for (int q = 0; q < 6; ++q) vb[q] = {0.f, 0.f};
-#pragma unroll
-        for (int q = 6; q < 12; ++q) va[q] = {0.f, 0.f};
-      } else {
-        ld_half32(a.x[p], fx, ci, s == 0 ? a.Ls - 1 : s - 1, i, 0, va);
-        ld_half32(a.x[p], fx, ci, s == a.Ls - 1 ? 0 : s + 1, i, 1, vb);
-#pragma unroll
-        for (int q = 0; q < 6; ++q) vb[q] = {0.f, 0.f};
-#pragma unroll
-        for (int q = 6; q < 12; ++q) va[q] = {0.f, 0.f};
-      }
-#pragma unroll
-      for (int cc = 0; cc < WG_CB; ++cc) {
-        if (cc >= nco) break;
-        float sr0 = 0.f, si0 = 0.f, sr1 = 0.f, si1 = 0.f;
-#pragma unroll
-        for (int q = 0; q < 12; ++q) {  // g * conj(v)
-          sr0 = fmaf(g[cc][q].r, va[q].r, fmaf(g[cc][q].i, va[q].i, sr0));
-          si0 = fmaf(g[cc][q].i, va[q].r, fmaf(-g[cc][q].r, va[q].i, si0));
-          sr1 = fmaf(g[cc][q].r, vb[q].r, fmaf(g[cc][q].i, vb[q].i, sr1));
-          si1 = fmaf(g[cc][q].i, vb[q].r, fmaf(-g[cc][q].r, vb[q].i, si1));
+        for (int cc = 0; cc < CB; ++cc) {
+          wg_acc(g[cc], v, acc[cc][k][2 * d], 0, 12);
+          wg_acc(g[cc], gv, acc[cc][k][2 * d + 1], 0, 12);
         }
-        ar[cc][ci][0] += sr0;
-        ai[cc][ci][0] += si0;
-        ar[cc][ci][1] += sr1;
-        ai[cc][ci][1] += si1;
+      }
+    }
+    // set 0 the same-site chirality halves, set 1 those of the s neighbours
+    const int sm = s == 0 ? a.Ls - 1 : s - 1, sp = s == a.Ls - 1 ? 0 : s + 1;
+#pragma unroll
+    for (int k = 0; k < CI; ++k) {
+      const int ci = min(ci0 + k, a.Cin - 1);
+      cx<float> v[12];
+      ld_half32(a.x[p], fx, ci, SET == 0 ? s : sm, i, 0, v);
+      ld_half32(a.x[p], fx, ci, SET == 0 ? s : sp, i, 1, v);
+#pragma unroll
+      for (int cc = 0; cc < CB; ++cc) {
+        wg_acc(g[cc], v, acc[cc][k][8], 0, 6);
+        wg_acc(g[cc], v, acc[cc][k][9], 6, 12);
       }
     }
   }
-  // reduce the WG_CB x C_in x 2 complex sums over the work-group
-  constexpr int NV = 2 * WG_CB * NET_MAXC * 2;  // (cc, ci, h, comp)
-  __shared__ double red[4][NV];
+  // FP64 sums over the wave, then over the work-group
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  constexpr int NV = CB * CI * NT * 2;
 #pragma unroll
-  for (int cc = 0; cc < WG_CB; ++cc)
+  for (int cc = 0; cc < CB; ++cc)
 #pragma unroll
-    for (int ci = 0; ci < NET_MAXC; ++ci)
+    for (int k = 0; k < CI; ++k)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if (cc >= nco || ci >= a.Cin) continue;
-        double vr = ar[cc][ci][h], vi = ai[cc][ci][h];
+      for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-          vr += __shfl_xor(vr, off, 64);
-          vi += __shfl_xor(vi, off, 64);
+        for (int h = 0; h < 2; ++h) {
+          double v = acc[cc][k][t][h];
+#pragma unroll
+          for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+          if (lane == 0) dred[wv * NV + ((cc * CI + k) * NT + t) * 2 + h] = v;
         }
-        if (lane == 0) {
-          const int k = ((cc * NET_MAXC + ci) * 2 + h) * 2;
-          red[wv][k] = vr;
-          red[wv][k + 1] = vi;
-        }
-      }
   __syncthreads();
-  const int k = threadIdx.x;
-  if (k < NV) {
-    const int comp = k & 1, h = (k >> 1) & 1, ci = (k >> 2) % NET_MAXC, cc = (k >> 2) / NET_MAXC;
-    if (cc < nco && ci < a.Cin) {
-      double tsum = 0.0;
-      for (int w = 0; w < (int)(blockDim.x + 63) / 64; ++w) tsum += red[w][k];
-      const int t = grp < 8 ? (h ? 10 + grp : 2 + grp) : grp == 8 ? h : 18 + h;
-      const int y = t * a.Cin + ci, c = c0 + cc;
-      a.partial[((((size_t)y * 2 + p) * a.Cout + c) * gridDim.x + blockIdx.x) * 2 + comp] = tsum;
-    }
+  for (int k = threadIdx.x; k < NV; k += 256) {
+    const int comp = k & 1, t = (k >> 1) % NT, ch = (k >> 1) / NT, ci = ci0 + ch % CI, c = c0 + ch / CI;
+    if (ci >= a.Cin || c >= a.Cout) continue;
+    double tsum = 0.0;
+    for (int w = 0; w < 4; ++w) tsum += dred[w * NV + k];
+    // term index: transports 2 + e and 10 + e, then 0, 1 or 18, 19
+    const int d = t >> 1, e = 2 * SET + (d & 1) + 4 * (d >> 1);
+    const int term = t < 8 ? (t & 1 ? 10 + e : 2 + e) : t - 8 + 18 * SET;
+    const int y = term * a.Cin + ci;
+    a.partial[((((size_t)y * 2 + p) * a.Cout + c) * gridDim.x + blockIdx.x) * 2 + comp] = tsum;
   }
 }
 
-// gW[t][c][ci] (+)= sum over parity and blocks (fixed order), as (re, im) doubles
-__global__ void pt_wgrad_final(const double* partial, int Cin, int Cout, int nblk, int accumulate, double* gw) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;  // over NET_TERMS*Cout*Cin*2
+// grid: (blocks, 2 sets x channel blocks, parity)
+template <int CB, int CI>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) pt_wgrad_kernel(NetGradArgs a) {
+  __shared__ double red[4 * 4 * WG_TERMS * 2];
+  const int set = blockIdx.y & 1, blk = blockIdx.y >> 1, nci = (a.Cin + CI - 1) / CI;
+  const int c0 = blk / nci * CB, ci0 = blk % nci * CI, p = blockIdx.z;
+  if (set == 0)
+    wgrad_set<CB, CI, 0>(a, c0, ci0, p, red);
+  else
+    wgrad_set<CB, CI, 1>(a, c0, ci0, p, red);
+}
+
+// gW[t][c][ci] (+)= sum over parity and blocks as (re, im) doubles: one wave per
+// value, lanes over the blocks, then across the lanes (a fixed order)
+__global__ void __launch_bounds__(256) pt_wgrad_final(const double* partial, int Cin, int Cout, int nblk,
+                                                      int accumulate, double* gw) {
+  const int k = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;  // over NET_TERMS*Cout*Cin*2
   if (k >= NET_TERMS * Cout * Cin * 2) return;
   const int comp = k & 1, rest = k >> 1;
   const int ci = rest % Cin, c = (rest / Cin) % Cout, t = rest / (Cin * Cout);
   const int y = t * Cin + ci;
   double s = 0.0;
   for (int p = 0; p < 2; ++p)
-    for (int b = 0; b < nblk; ++b) s += partial[((((size_t)y * 2 + p) * Cout + c) * nblk + b) * 2 + comp];
-  gw[k] = accumulate ? gw[k] + s : s;
+    for (int b = lane; b < nblk; b += 64) s += partial[((((size_t)y * 2 + p) * Cout + c) * nblk + b) * 2 + comp];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (lane == 0) gw[k] = accumulate ? gw[k] + s : s;
 }
 
 // residual loss: partial sums of <a, r> (re, im) and |a|^2 over one-channel
@@ -1011,12 +1022,23 @@ void launch_pt_layer(const NetLayerArgs& a, bool adj, hipStream_t st) {
     launch_pt_layer_cb<4, true>(a, adj, st);
 }
 
+template <int CB, int CI>
+void launch_wgrad_cb(const NetGradArgs& a, int nblk, hipStream_t st) {
+  const dim3 grid(nblk, 2 * ((a.Cout + CB - 1) / CB) * ((a.Cin + CI - 1) / CI), 2);
+  hipLaunchKernelGGL((pt_wgrad_kernel<CB, CI>), grid, dim3(256), 0, st, a);
+}
+
+// four outputs of one input per thread, unless there are fewer outputs
 void launch_pt_wgrad(const NetGradArgs& a, int nblk, int accumulate, double* gw, hipStream_t st) {
-  dim3 grid(nblk, WG_GROUPS * ((a.Cout + WG_CB - 1) / WG_CB), 2);
-  hipLaunchKernelGGL(pt_wgrad_kernel, grid, dim3(256), 0, st, a);
+  if (a.Cout == 1)
+    launch_wgrad_cb<1, 4>(a, nblk, st);
+  else if (a.Cout == 2)
+    launch_wgrad_cb<2, 2>(a, nblk, st);
+  else
+    launch_wgrad_cb<4, 1>(a, nblk, st);
   const int n = NET_TERMS * a.Cout * a.Cin * 2;
-  hipLaunchKernelGGL(pt_wgrad_final, dim3((n + 255) / 256), dim3(256), 0, st, a.partial, a.Cin, a.Cout, nblk,
-                     accumulate, gw);
+  hipLaunchKernelGGL(pt_wgrad_final, dim3((n + 3) / 4), dim3(256), 0, st, a.partial, a.Cin, a.Cout, nblk, accumulate,
+                     gw);
 }
 
 void launch_net_resid(int Vh, int Ls, const float* av, const float* rv, const double* rnorm, double* partial,

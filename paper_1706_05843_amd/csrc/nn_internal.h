@@ -26,6 +26,7 @@ struct NetGradArgs {
   const float* g[2];         // dL/dy* at the layer output, both parities, Cout channels
   const float* links[2];
   const int* nbr[2];
+  const int* order;          // [Vh] traversal position -> checkerboard index
   double* partial;           // [20*Cin][2][Cout][nblk][2]
   int Vh, Ls, Cin, Cout;
 };
