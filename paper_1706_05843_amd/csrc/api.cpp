@@ -611,7 +611,7 @@ int inner_iteration(eofa_ctx* C, const Form& F, int S, const HopArgs& k1, const 
   const DtArgs dt = dt_args(C, F, nrhs);
   if (ring) {
     launch_p_update(S, g, rin, ring->at(k), ring->at(k + 1), Sst.alpha, Sst.beta, Sst.u2run,
-                    ring->ahist + (size_t)(k % ring->R) * nrhs, nrhs, dt, st);
+                    ring->ahist + (size_t)(k % ring->R) * nrhs, ring->R, nrhs, dt, st);
     if ((k + 1) % ring->F == 0)
       launch_x_flush(S, g, xin, ring->base, ring->slot, (k + 1 - ring->F) % ring->R, ring->F, ring->R, ring->ahist,
                      nrhs, st);

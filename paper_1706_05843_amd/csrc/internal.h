@@ -165,8 +165,8 @@ struct DtArgs {
   double cpd = 0.0, cmd = 0.0;  // c+d, c-d
 };
 void launch_p_update(int ps, const Geometry& g, const void* r, const void* p, void* pn, const double* alpha,
-                     const double* beta, const int* u2run, double* ahist, int nrhs, const DtArgs& dt,
-                     hipStream_t st);
+                     const double* beta, const int* u2run, double* ahist, int R /* ring slots */, int nrhs,
+                     const DtArgs& dt, hipStream_t st);
 void launch_x_flush(int ps, const Geometry& g, void* x, const void* ring, size_t slot_bytes, int first, int nslots,
                     int R, const double* ahist, int nrhs, hipStream_t st);
 // fused CG update: x in sol_prec(ps), the residual in ps (the inner precision)

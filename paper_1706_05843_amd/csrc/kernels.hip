@@ -1881,10 +1881,13 @@ int launch_norm2(int prec, const Geometry& g, const void* f, int nrhs, double* p
 // p_{k+1} = r + beta p_k goes to the next ring slot, and the step's alpha is
 // kept (0 when the step did not run); a right-hand side whose CG has stopped
 // carries p forward, so the last direction is always in the newest slot.
+// nt (ring_streams): the old direction, read here for the last time before the
+// flush, and in the flush the ring and x, bypass the caches that hold the
+// fields of the next hops.
 template <int PS, int PR>
 __global__ void __launch_bounds__(256) p_update_kernel(int Ls, int Vh, int nrhs, const void* rr, const void* p,
                                                          void* pn, const double* alpha, const double* beta,
-                                                         const int* u2run, double* ahist) {
+                                                         const int* u2run, double* ahist, bool nt) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   const int r = blockIdx.y;
   if (idx >= Ls * Vh) return;
@@ -1895,7 +1898,10 @@ __global__ void __launch_bounds__(256) p_update_kernel(int Ls, int Vh, int nrhs,
   using RR = typename ST<PR>::R;
   using RS = typename ST<PS>::R;
   cx<RS> pv[12];
-  ld_spinor<PS>(p, f, r, s, i, pv);
+  if (nt)
+    ld_spinor_nt<PS>(p, f, r, s, i, pv);
+  else
+    ld_spinor<PS>(p, f, r, s, i, pv);
   if (run) {
     cx<RR> rv[12];
     ld_spinor_nt<PR>(rr, f, r, s, i, rv);
@@ -1912,7 +1918,7 @@ __global__ void __launch_bounds__(256) p_update_kernel(int Ls, int Vh, int nrhs,
 template <int PS, int PR>
 __global__ void __launch_bounds__(256) x_flush_kernel(int Ls, int Vh, int nrhs, void* x, const char* ring,
                                                         size_t slot_bytes, int first, int nslots, int R,
-                                                        const double* ahist) {
+                                                        const double* ahist, bool nt) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   const int r = blockIdx.y;
   if (idx >= Ls * Vh) return;
@@ -1927,7 +1933,10 @@ __global__ void __launch_bounds__(256) x_flush_kernel(int Ls, int Vh, int nrhs, 
     const RR a = (RR)ahist[(size_t)slot * nrhs + r];
     if (a == RR(0)) continue;
     cx<RS> pv[12];
-    ld_spinor<PS>(ring + slot * slot_bytes, f, r, s, i, pv);
+    if (nt)
+      ld_spinor_nt<PS>(ring + slot * slot_bytes, f, r, s, i, pv);
+    else
+      ld_spinor<PS>(ring + slot * slot_bytes, f, r, s, i, pv);
 #pragma unroll
     for (int c = 0; c < 12; ++c) {
       xv[c].r = fma(a, (RR)pv[c].r, xv[c].r);
@@ -1974,7 +1983,7 @@ template <int PS, int PR, int RL>
 __global__ void __launch_bounds__(256) p_update_dt_kernel(int Ls, int Vh, int nrhs, const void* rr, const void* p,
                                                             void* pn, const double* alpha, const double* beta,
                                                             const int* u2run, double* ahist, double cpd, double cmd,
-                                                            const double* mop) {
+                                                            const double* mop, bool nt) {
   const int r = blockIdx.y;
   const ColLane cl = col_lane(Ls, Vh);
   const bool run = u2run[r] != 0;  // uniform over the grid
@@ -1985,7 +1994,12 @@ __global__ void __launch_bounds__(256) p_update_dt_kernel(int Ls, int Vh, int nr
   cx<RS> pv[12];
 #pragma unroll
   for (int c = 0; c < 12; ++c) pv[c] = {RS(0), RS(0)};
-  if (cl.live) ld_spinor<PS>(p, f, r, cl.s, cl.i, pv);
+  if (cl.live) {
+    if (nt)
+      ld_spinor_nt<PS>(p, f, r, cl.s, cl.i, pv);
+    else
+      ld_spinor<PS>(p, f, r, cl.s, cl.i, pv);
+  }
   if (run) {
     cx<RR> rv[12];
 #pragma unroll
@@ -2040,13 +2054,13 @@ __global__ void __launch_bounds__(256) cg_update_dt_kernel(int Ls, int Vh, int n
 
 template <int PS, int PR>
 void launch_p_update_dt(const Geometry& g, const void* r, const void* p, void* pn, const double* alpha,
-                        const double* beta, const int* u2run, double* ahist, int nrhs, const DtArgs& dt,
+                        const double* beta, const int* u2run, double* ahist, int nrhs, const DtArgs& dt, bool nt,
                         hipStream_t st) {
   const int G = 64 / g.Ls;
   dim3 grid((g.Vh + 4 * G - 1) / (4 * G), nrhs);
   auto fn = g.Ls == 16 ? p_update_dt_kernel<PS, PR, 16> : p_update_dt_kernel<PS, PR, 0>;
   hipLaunchKernelGGL(fn, grid, dim3(256), 0, st, g.Ls, g.Vh, nrhs, r, p, pn, alpha, beta, u2run, ahist, dt.cpd,
-                     dt.cmd, dt.mop);
+                     dt.cmd, dt.mop, nt);
 }
 
 template <int PS, int PX, int PR>
@@ -2059,41 +2073,52 @@ void launch_cg_update_dt(const Geometry& g, void* x, const void* r, void* p, con
                      dt.mop);
 }
 
+// Whether the ring of directions is past what the 256 MB MALL can hold until its
+// flush. FP16S solve of 16^3 x 32 x 16 (16 slots of 54 MB), with and without the
+// bypass: 245.5 and 258.2 ms (the update 31 -> 25 us; plain accesses to the
+// residual in K4 and the update instead cost 6 %, streaming the new direction
+// 2 %).
+static bool ring_streams(int ps, const Geometry& g, int nrhs, int R) {
+  return (size_t)R * packed_bytes(ps, g, nrhs) > (size_t(256) << 20);
+}
+
 void launch_p_update(int ps, const Geometry& g, const void* r, const void* p, void* pn, const double* alpha,
-                     const double* beta, const int* u2run, double* ahist, int nrhs, const DtArgs& dt,
+                     const double* beta, const int* u2run, double* ahist, int R, int nrhs, const DtArgs& dt,
                      hipStream_t st) {
+  const bool nt = ring_streams(ps, g, nrhs, R);
   if (dt.mop) {
     if (ps == P64)
-      launch_p_update_dt<P64, P64>(g, r, p, pn, alpha, beta, u2run, ahist, nrhs, dt, st);
+      launch_p_update_dt<P64, P64>(g, r, p, pn, alpha, beta, u2run, ahist, nrhs, dt, nt, st);
     else if (ps == P32)
-      launch_p_update_dt<P32, P32>(g, r, p, pn, alpha, beta, u2run, ahist, nrhs, dt, st);
+      launch_p_update_dt<P32, P32>(g, r, p, pn, alpha, beta, u2run, ahist, nrhs, dt, nt, st);
     else
-      launch_p_update_dt<P16, P16>(g, r, p, pn, alpha, beta, u2run, ahist, nrhs, dt, st);
+      launch_p_update_dt<P16, P16>(g, r, p, pn, alpha, beta, u2run, ahist, nrhs, dt, nt, st);
     return;
   }
   if (ps == P64)
     hipLaunchKernelGGL((p_update_kernel<P64, P64>), EOFA_EW_GRID, g.Ls, g.Vh, nrhs, r, p, pn, alpha, beta, u2run,
-                       ahist);
+                       ahist, nt);
   else if (ps == P32)
     hipLaunchKernelGGL((p_update_kernel<P32, P32>), EOFA_EW_GRID, g.Ls, g.Vh, nrhs, r, p, pn, alpha, beta, u2run,
-                       ahist);
+                       ahist, nt);
   else
     hipLaunchKernelGGL((p_update_kernel<P16, P16>), EOFA_EW_GRID, g.Ls, g.Vh, nrhs, r, p, pn, alpha, beta, u2run,
-                       ahist);
+                       ahist, nt);
 }
 
 void launch_x_flush(int ps, const Geometry& g, void* x, const void* ring, size_t slot_bytes, int first, int nslots,
                     int R, const double* ahist, int nrhs, hipStream_t st) {
   const char* rg = (const char*)ring;
+  const bool nt = ring_streams(ps, g, nrhs, R);
   if (ps == P64)
     hipLaunchKernelGGL((x_flush_kernel<P64, P64>), EOFA_EW_GRID, g.Ls, g.Vh, nrhs, x, rg, slot_bytes, first, nslots,
-                       R, ahist);
+                       R, ahist, nt);
   else if (ps == P32)
     hipLaunchKernelGGL((x_flush_kernel<P32, P32>), EOFA_EW_GRID, g.Ls, g.Vh, nrhs, x, rg, slot_bytes, first, nslots,
-                       R, ahist);
+                       R, ahist, nt);
   else
     hipLaunchKernelGGL((x_flush_kernel<P16, P32>), EOFA_EW_GRID, g.Ls, g.Vh, nrhs, x, rg, slot_bytes, first, nslots,
-                       R, ahist);
+                       R, ahist, nt);
 }
 
 void launch_cg_update(int ps, const Geometry& g, void* x, const void* r, void* p, const double* alpha,
