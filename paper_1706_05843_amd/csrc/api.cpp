@@ -244,7 +244,14 @@ HopArgs base_args(eofa_ctx* C, int prec, int out_parity, int nrhs) {
   a.Vh = C->g.Vh;
   a.Ls = C->g.Ls;
   a.nrhs = nrhs;
-  a.rhs_block = nrhs;
+  // right-hand sides per work-group where the autotuner has not chosen: all of
+  // them share the staged links; but in FP64 and FP32, when one field's input and
+  // output exceed the 256 MB MALL, a long loop over right-hand sides drifts the
+  // work-groups of an XCD apart and its L2 loses the columns they share. Dslash,
+  // 24^3 x 64 x 12, by right-hand sides per work-group: 12 x FP32 1: 4839 us,
+  // 2: 4612, 3: 4675, 12: 5030; 3 x FP64 2: 2688, 3: 2779; 4 x FP16S 2: 902,
+  // 4: 887; within the MALL (16^3 x 32 x 16, 4 x FP32) 2: 305, 4: 305.
+  a.rhs_block = prec != P16 && 2 * packed_bytes(prec, C->g, 1) > (size_t(256) << 20) ? std::min(nrhs, 2) : nrhs;
   a.W = default_waves(C->g.Ls);
   auto it = C->tuned.find(prec * 4096 + nrhs);
   if (it != C->tuned.end()) {
