@@ -122,6 +122,7 @@ template <int P, int ROLE>
 __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
   using RT = RoleT<ROLE>;
   using R = typename ST<P>::R;
+  constexpr bool FIN = ROLE == ROLE_K3 || ROLE == ROLE_D3 || ROLE == ROLE_K1T || ROLE == ROLE_D1;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   cx<R>* s_g = (cx<R>*)smem;  // [direction][component of the half spinor][lane]
   __shared__ double s_red[SMW];
@@ -131,20 +132,23 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int g = lane / Ls, s = lane - g * Ls, r = blockIdx.y;
   // a contiguous run of tiles per XCD (work-groups are dealt round-robin)
-  const int nblk = gridDim.x, xcd = blockIdx.x % 8;
+  const int nblk = (Vh + G - 1) / G, xcd = blockIdx.x % 8;
+  // a CG step on the previous launch's partial sums (K3: alpha, K1: beta) runs in
+  // a work-group of its own beside the tiles; the others may see a halt flag
+  // before or after it is set, and either is right (a right-hand side halted by
+  // this step is not used by the next launch)
+  if ((int)blockIdx.x == nblk) {
+    if constexpr (FIN) fin_block(a.fin_mode, a.fin_partial + (size_t)r * a.fin_nblk, a.fin_nblk, a.fin_S, r, s_red);
+    return;
+  }
   const int tile = xcd * (nblk / 8) + min(xcd, nblk % 8) + blockIdx.x / 8;
   const int kk = tile * G + g;
   const bool live = g < G && kk < Vh;
   const FD fd = {Ls, Vh, a.nrhs};
-  // the previous launch's partial sums and the CG step they feed (as in the
-  // general kernel): only work-group 0 writes the CG state
-  if constexpr (ROLE == ROLE_K3 || ROLE == ROLE_D3)
-    if (a.fin_partial != nullptr && blockIdx.x == 0)
-      fin_block(a.fin_mode, a.fin_partial + (size_t)r * a.fin_nblk, a.fin_nblk, a.fin_S, r, s_red);
   // one read of the halt flag per work-group: every wave takes the same branch
   if (a.halt != nullptr && tid == 0)
     s_halt = __hip_atomic_load(a.halt + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const int site = a.order[min(kk, Vh - 1)];
+  const int site = min(kk, Vh - 1);  // checkerboard order: a table lookup less in front of the gather
   const int n = a.nbr[(size_t)site * 8 + wave];
   cx<R> U[9];
 #pragma unroll
@@ -322,7 +326,7 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
     if (tid == 0) {
       double t = 0.0;
       for (int k = 0; k < 6; ++k) t += s_red[k];
-      a.partial[(size_t)r * gridDim.x + blockIdx.x] = t;
+      a.partial[(size_t)r * nblk + blockIdx.x] = t;
     }
   }
 }
@@ -331,7 +335,8 @@ template <int P, int ROLE>
 int launch_small_t(const HopArgs& a, hipStream_t st) {
   const int G = 64 / a.Ls;
   const size_t lds = sizeof(cx<typename ST<P>::R>) * SMW * 6 * 64;  // 48 KiB in FP64
-  hipLaunchKernelGGL((hop_small_kernel<P, ROLE>), dim3((a.Vh + G - 1) / G, a.nrhs), dim3(64 * SMW), lds, st, a);
+  hipLaunchKernelGGL((hop_small_kernel<P, ROLE>), dim3((a.Vh + G - 1) / G + (a.fin_partial ? 1 : 0), a.nrhs),
+                     dim3(64 * SMW), lds, st, a);
   return hipGetLastError() == hipSuccess ? EOFA_OK : EOFA_ERR_HIP;
 }
 

@@ -164,14 +164,22 @@ struct DtArgs {
   const double* mop = nullptr;  // [nrhs] operator mass; nullptr: plain update
   double cpd = 0.0, cmd = 0.0;  // c+d, c-d
 };
+// partial sums an update reduces itself (small lattices), else null: see beta_step
+struct BetaStep {
+  const double* partial = nullptr;  // [nrhs][nblk] of |r|^2
+  int nblk = 0;
+  const double* rr = nullptr;  // CgState fields, as before the step
+  const int* halt = nullptr;
+};
 void launch_p_update(int ps, const Geometry& g, const void* r, const void* p, void* pn, const double* alpha,
                      const double* beta, const int* u2run, double* ahist, int R /* ring slots */, int nrhs,
-                     const DtArgs& dt, hipStream_t st);
+                     const DtArgs& dt, const BetaStep& bs, hipStream_t st);
 void launch_x_flush(int ps, const Geometry& g, void* x, const void* ring, size_t slot_bytes, int first, int nslots,
                     int R, const double* ahist, int nrhs, hipStream_t st);
 // fused CG update: x in sol_prec(ps), the residual in ps (the inner precision)
 void launch_cg_update(int ps, const Geometry& g, void* x, const void* r, void* p, const double* alpha,
-                      const double* beta, const int* u2run, int nrhs, const DtArgs& dt, hipStream_t st);
+                      const double* beta, const int* u2run, int nrhs, const DtArgs& dt, const BetaStep& bs,
+                      hipStream_t st);
 void launch_finalize(int mode, const double* partial, int nblk, int nrhs, CgState st_, double* out,
                      hipStream_t st);
 

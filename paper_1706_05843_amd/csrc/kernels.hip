@@ -1278,9 +1278,9 @@ constexpr int acc_prec() {
 
 // Launches whose tiles of one wave leave most of the chip idle go to the kernel
 // of hop_small.hip, which shares each tile among eight waves. Time per FP64 /
-// FP32 CG iteration there and here (us): 16 tiles (4^4, Ls = 8) 34 and 57 / 31
-// and 47; 256 (8^4) 40 and 65 / 33 and 52; 512 53 and 74 / 38 and 57; 820 (Ls =
-// 12) 86 and 89 / 54 and 64; 1024 91 and 98 / 54 and 70; 2048 167 and 144 / 86
+// FP32 CG iteration there and here (us): 16 tiles (4^4, Ls = 8) 32 and 57 / 27
+// and 47; 256 (8^4) 39 and 65 / 30 and 52; 512 51 and 74 / 35 and 57; 820 (Ls =
+// 12) 86 and 89 / 53 and 64; 1024 91 and 98 / 52 and 70; 2048 167 and 144 / 86
 // and 88, at Ls = 16, whose row form here is faster, 180 and 129 / 93 and 71.
 // The single hop in FP64 is level at 820.
 bool hop_is_small(int prec, int Vh, int Ls, int nrhs) {
@@ -1805,14 +1805,38 @@ __global__ void __launch_bounds__(256) norm2_kernel(int Ls, int Vh, int nrhs, co
   block_sum_store(n, partial + (size_t)r * gridDim.x + blockIdx.x);
 }
 
+// The beta step of an update. On small lattices (BetaStep.partial set) every
+// work-group sums the residual's partials itself instead of waiting for a
+// finalize launch; the CG state is left as it is, and the next K1 takes the
+// step on it (FIN_BETA). Else beta and the run flag are read. All threads of the
+// work-group take part; returns whether the step runs.
+__device__ __forceinline__ bool beta_step(const BetaStep& b, const double* beta, const int* u2run, int r, double& be) {
+  if (b.partial == nullptr) {
+    be = beta[r];
+    return u2run[r] != 0;
+  }
+  __shared__ double red[4];
+  const double* pr = b.partial + (size_t)r * b.nblk;
+  double t = 0.0;
+  for (int j = threadIdx.x; j < b.nblk; j += 256) t += pr[j];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+  __syncthreads();
+  const double sum = (red[0] + red[1]) + (red[2] + red[3]);
+  be = sum / b.rr[r];
+  return b.halt[r] == 0 && isfinite(sum);
+}
+
 // x += alpha p;  p = r + beta p   (CG, after the residual update; x in PX,
 // the residual in PR)
 template <int PS, int PX, int PR>
 __global__ void __launch_bounds__(256) cg_update_kernel(int Ls, int Vh, int nrhs, void* x, const void* rr, void* p, const double* alpha,
-                                 const double* beta, const int* u2run) {
+                                 const double* beta, const int* u2run, BetaStep bs) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   const int r = blockIdx.y;
-  if (idx >= Ls * Vh || u2run[r] == 0) return;
+  double be_r;
+  if (!beta_step(bs, beta, u2run, r, be_r) || idx >= Ls * Vh) return;
   const int i = idx / Ls, s = idx - i * Ls;
   const FD f = {Ls, Vh, nrhs};
   using RR = typename ST<PX>::R;
@@ -1822,7 +1846,7 @@ __global__ void __launch_bounds__(256) cg_update_kernel(int Ls, int Vh, int nrhs
   ld_spinor<PS>(p, f, r, s, i, pv);  // p is re-read by the next hop's neighbours: cached
   ld_spinor_nt<PX>(x, f, r, s, i, xv);
   ld_spinor_nt<PR>(rr, f, r, s, i, rv);
-  const RR al = (RR)alpha[r], be = (RR)beta[r];
+  const RR al = (RR)alpha[r], be = (RR)be_r;
   cx<RS> pn[12];
 #pragma unroll
   for (int c = 0; c < 12; ++c) {
@@ -1887,11 +1911,12 @@ int launch_norm2(int prec, const Geometry& g, const void* f, int nrhs, double* p
 template <int PS, int PR>
 __global__ void __launch_bounds__(256) p_update_kernel(int Ls, int Vh, int nrhs, const void* rr, const void* p,
                                                          void* pn, const double* alpha, const double* beta,
-                                                         const int* u2run, double* ahist, bool nt) {
+                                                         const int* u2run, double* ahist, bool nt, BetaStep bs) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   const int r = blockIdx.y;
+  double be_r;
+  const bool run = beta_step(bs, beta, u2run, r, be_r);
   if (idx >= Ls * Vh) return;
-  const bool run = u2run[r] != 0;
   if (idx == 0) ahist[r] = run ? alpha[r] : 0.0;
   const int i = idx / Ls, s = idx - i * Ls;
   const FD f = {Ls, Vh, nrhs};
@@ -1905,7 +1930,7 @@ __global__ void __launch_bounds__(256) p_update_kernel(int Ls, int Vh, int nrhs,
   if (run) {
     cx<RR> rv[12];
     ld_spinor_nt<PR>(rr, f, r, s, i, rv);
-    const RR be = (RR)beta[r];
+    const RR be = (RR)be_r;
 #pragma unroll
     for (int c = 0; c < 12; ++c) pv[c] = {(RS)fma(be, (RR)pv[c].r, rv[c].r), (RS)fma(be, (RR)pv[c].i, rv[c].i)};
   }
@@ -1983,10 +2008,11 @@ template <int PS, int PR, int RL>
 __global__ void __launch_bounds__(256) p_update_dt_kernel(int Ls, int Vh, int nrhs, const void* rr, const void* p,
                                                             void* pn, const double* alpha, const double* beta,
                                                             const int* u2run, double* ahist, double cpd, double cmd,
-                                                            const double* mop, bool nt) {
+                                                            const double* mop, bool nt, BetaStep bs) {
   const int r = blockIdx.y;
   const ColLane cl = col_lane(Ls, Vh);
-  const bool run = u2run[r] != 0;  // uniform over the grid
+  double be_r;
+  const bool run = beta_step(bs, beta, u2run, r, be_r);  // uniform over the grid
   if (blockIdx.x == 0 && threadIdx.x == 0) ahist[r] = run ? alpha[r] : 0.0;
   const FD f = {Ls, Vh, nrhs};
   using RR = typename ST<PR>::R;
@@ -2006,7 +2032,7 @@ __global__ void __launch_bounds__(256) p_update_dt_kernel(int Ls, int Vh, int nr
     for (int c = 0; c < 12; ++c) rv[c] = {RR(0), RR(0)};
     if (cl.live) ld_spinor_nt<PR>(rr, f, r, cl.s, cl.i, rv);
     dt_apply<RR, RL>(rv, cl.s, cl.g, Ls, (RR)cpd, (RR)cmd, (RR)mop[r]);
-    const RR be = (RR)beta[r];
+    const RR be = (RR)be_r;
 #pragma unroll
     for (int c = 0; c < 12; ++c) pv[c] = {(RS)fma(be, (RR)pv[c].r, rv[c].r), (RS)fma(be, (RR)pv[c].i, rv[c].i)};
   }
@@ -2018,9 +2044,10 @@ template <int PS, int PX, int PR, int RL>
 __global__ void __launch_bounds__(256) cg_update_dt_kernel(int Ls, int Vh, int nrhs, void* x, const void* rr,
                                                              void* p, const double* alpha, const double* beta,
                                                              const int* u2run, double cpd, double cmd,
-                                                             const double* mop) {
+                                                             const double* mop, BetaStep bs) {
   const int r = blockIdx.y;
-  if (u2run[r] == 0) return;  // uniform over the block
+  double be_r;
+  if (!beta_step(bs, beta, u2run, r, be_r)) return;  // uniform over the block
   const ColLane cl = col_lane(Ls, Vh);
   const FD f = {Ls, Vh, nrhs};
   using RR = typename ST<PX>::R;
@@ -2039,7 +2066,7 @@ __global__ void __launch_bounds__(256) cg_update_dt_kernel(int Ls, int Vh, int n
   dt_apply<RR, RL>(rv, cl.s, cl.g, Ls, (RR)cpd, (RR)cmd, (RR)mop[r]);
   if (!cl.live) return;
   ld_spinor_nt<PX>(x, f, r, cl.s, cl.i, xv);
-  const RR al = (RR)alpha[r], be = (RR)beta[r];
+  const RR al = (RR)alpha[r], be = (RR)be_r;
   cx<RS> pn[12];
 #pragma unroll
   for (int c = 0; c < 12; ++c) {
@@ -2055,22 +2082,23 @@ __global__ void __launch_bounds__(256) cg_update_dt_kernel(int Ls, int Vh, int n
 template <int PS, int PR>
 void launch_p_update_dt(const Geometry& g, const void* r, const void* p, void* pn, const double* alpha,
                         const double* beta, const int* u2run, double* ahist, int nrhs, const DtArgs& dt, bool nt,
-                        hipStream_t st) {
+                        const BetaStep& bs, hipStream_t st) {
   const int G = 64 / g.Ls;
   dim3 grid((g.Vh + 4 * G - 1) / (4 * G), nrhs);
   auto fn = g.Ls == 16 ? p_update_dt_kernel<PS, PR, 16> : p_update_dt_kernel<PS, PR, 0>;
   hipLaunchKernelGGL(fn, grid, dim3(256), 0, st, g.Ls, g.Vh, nrhs, r, p, pn, alpha, beta, u2run, ahist, dt.cpd,
-                     dt.cmd, dt.mop, nt);
+                     dt.cmd, dt.mop, nt, bs);
 }
 
 template <int PS, int PX, int PR>
 void launch_cg_update_dt(const Geometry& g, void* x, const void* r, void* p, const double* alpha,
-                         const double* beta, const int* u2run, int nrhs, const DtArgs& dt, hipStream_t st) {
+                         const double* beta, const int* u2run, int nrhs, const DtArgs& dt, const BetaStep& bs,
+                         hipStream_t st) {
   const int G = 64 / g.Ls;
   dim3 grid((g.Vh + 4 * G - 1) / (4 * G), nrhs);
   auto fn = g.Ls == 16 ? cg_update_dt_kernel<PS, PX, PR, 16> : cg_update_dt_kernel<PS, PX, PR, 0>;
   hipLaunchKernelGGL(fn, grid, dim3(256), 0, st, g.Ls, g.Vh, nrhs, x, r, p, alpha, beta, u2run, dt.cpd, dt.cmd,
-                     dt.mop);
+                     dt.mop, bs);
 }
 
 // Whether the ring of directions is past what the 256 MB MALL can hold until its
@@ -2084,26 +2112,26 @@ static bool ring_streams(int ps, const Geometry& g, int nrhs, int R) {
 
 void launch_p_update(int ps, const Geometry& g, const void* r, const void* p, void* pn, const double* alpha,
                      const double* beta, const int* u2run, double* ahist, int R, int nrhs, const DtArgs& dt,
-                     hipStream_t st) {
+                     const BetaStep& bs, hipStream_t st) {
   const bool nt = ring_streams(ps, g, nrhs, R);
   if (dt.mop) {
     if (ps == P64)
-      launch_p_update_dt<P64, P64>(g, r, p, pn, alpha, beta, u2run, ahist, nrhs, dt, nt, st);
+      launch_p_update_dt<P64, P64>(g, r, p, pn, alpha, beta, u2run, ahist, nrhs, dt, nt, bs, st);
     else if (ps == P32)
-      launch_p_update_dt<P32, P32>(g, r, p, pn, alpha, beta, u2run, ahist, nrhs, dt, nt, st);
+      launch_p_update_dt<P32, P32>(g, r, p, pn, alpha, beta, u2run, ahist, nrhs, dt, nt, bs, st);
     else
-      launch_p_update_dt<P16, P16>(g, r, p, pn, alpha, beta, u2run, ahist, nrhs, dt, nt, st);
+      launch_p_update_dt<P16, P16>(g, r, p, pn, alpha, beta, u2run, ahist, nrhs, dt, nt, bs, st);
     return;
   }
   if (ps == P64)
     hipLaunchKernelGGL((p_update_kernel<P64, P64>), EOFA_EW_GRID, g.Ls, g.Vh, nrhs, r, p, pn, alpha, beta, u2run,
-                       ahist, nt);
+                       ahist, nt, bs);
   else if (ps == P32)
     hipLaunchKernelGGL((p_update_kernel<P32, P32>), EOFA_EW_GRID, g.Ls, g.Vh, nrhs, r, p, pn, alpha, beta, u2run,
-                       ahist, nt);
+                       ahist, nt, bs);
   else
     hipLaunchKernelGGL((p_update_kernel<P16, P16>), EOFA_EW_GRID, g.Ls, g.Vh, nrhs, r, p, pn, alpha, beta, u2run,
-                       ahist, nt);
+                       ahist, nt, bs);
 }
 
 void launch_x_flush(int ps, const Geometry& g, void* x, const void* ring, size_t slot_bytes, int first, int nslots,
@@ -2122,25 +2150,26 @@ void launch_x_flush(int ps, const Geometry& g, void* x, const void* ring, size_t
 }
 
 void launch_cg_update(int ps, const Geometry& g, void* x, const void* r, void* p, const double* alpha,
-                      const double* beta, const int* u2run, int nrhs, const DtArgs& dt, hipStream_t st) {
+                      const double* beta, const int* u2run, int nrhs, const DtArgs& dt, const BetaStep& bs,
+                      hipStream_t st) {
   if (dt.mop) {
     if (ps == P64)
-      launch_cg_update_dt<P64, P64, P64>(g, x, r, p, alpha, beta, u2run, nrhs, dt, st);
+      launch_cg_update_dt<P64, P64, P64>(g, x, r, p, alpha, beta, u2run, nrhs, dt, bs, st);
     else if (ps == P32)
-      launch_cg_update_dt<P32, P32, P32>(g, x, r, p, alpha, beta, u2run, nrhs, dt, st);
+      launch_cg_update_dt<P32, P32, P32>(g, x, r, p, alpha, beta, u2run, nrhs, dt, bs, st);
     else
-      launch_cg_update_dt<P16, P32, P16>(g, x, r, p, alpha, beta, u2run, nrhs, dt, st);
+      launch_cg_update_dt<P16, P32, P16>(g, x, r, p, alpha, beta, u2run, nrhs, dt, bs, st);
     return;
   }
   if (ps == P64)
     hipLaunchKernelGGL((cg_update_kernel<P64, P64, P64>), EOFA_EW_GRID, g.Ls, g.Vh, nrhs, x, r, p, alpha, beta,
-                       u2run);
+                       u2run, bs);
   else if (ps == P32)
     hipLaunchKernelGGL((cg_update_kernel<P32, P32, P32>), EOFA_EW_GRID, g.Ls, g.Vh, nrhs, x, r, p, alpha, beta,
-                       u2run);
+                       u2run, bs);
   else
     hipLaunchKernelGGL((cg_update_kernel<P16, P32, P16>), EOFA_EW_GRID, g.Ls, g.Vh, nrhs, x, r, p, alpha, beta,
-                       u2run);
+                       u2run, bs);
 }
 #undef EOFA_EW_GRID
 
