@@ -1349,14 +1349,14 @@ size_t hop_lds_bytes(int prec, int role, int Ls, int W) {
 // Whether a launch writes its output with non-temporal stores: when input and
 // output together exceed the 256 MB MALL the next kernel finds nothing of the
 // output on the chip, and the store only evicts neighbour spinors this kernel
-// still gathers from L2. One right-hand side, one box: FP64 16^3 x 32 x 16
-// 169 -> 153 us, FP64 24^3 x 64 x 12 907 -> 862, FP32 411 -> 401. FP16S stays
-// with plain stores: level beyond the MALL, 5 % slower on the 16^3 x 32 x 16
-// solve, whose next kernel reads the output there. Several right-hand sides
-// gained nothing (12 x FP32: 5020 -> 5064 us).
+// still gathers from L2. One box: FP64 16^3 x 32 x 16 169 -> 153 us, FP64
+// 24^3 x 64 x 12 907 -> 862, FP32 411 -> 401, 12 x FP32 (two right-hand sides per
+// work-group) 4590 -> 4426. FP16S stays with plain stores: level beyond the MALL,
+// 5 % slower on the 16^3 x 32 x 16 solve, whose next kernel reads the output
+// there.
 bool stream_output(int prec, const HopArgs& a) {
   const size_t site = prec == P64 ? 192 : 96;
-  return prec != P16 && a.nrhs == 1 && 2 * site * a.Vh * a.Ls > (size_t(256) << 20);
+  return prec != P16 && 2 * site * a.Vh * a.Ls > (size_t(256) << 20);
 }
 
 template <int P, int ROLE>
