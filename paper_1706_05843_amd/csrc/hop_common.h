@@ -89,6 +89,30 @@ __device__ __forceinline__ R dtinv_norm(R cpd, R cmd, R m, int Ls) {
   return recip(cpd * (R(1) + m * power_ls(cmd * recip(cpd), Ls)));
 }
 
+typedef _Float16 h4_t __attribute__((ext_vector_type(4)));
+typedef float f4_t __attribute__((ext_vector_type(4)));
+typedef unsigned u2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ h4_t h4_of(unsigned lo, unsigned hi) { return __builtin_bit_cast(h4_t, u2_t{lo, hi}); }
+__device__ __forceinline__ h4_t h4_of(h2_t lo, h2_t hi) { return __builtin_shufflevector(lo, hi, 0, 1, 2, 3); }
+
+// the two projected half spinors h[0..2], h[3..5] times the rows of U that this
+// lane holds: A00, A01 of colours 0 and 1, A10, A11 of colour 2
+__device__ __forceinline__ void su3_mfma_rows(h4_t A00, h4_t A01, h4_t A10, h4_t A11, const h2_t* h, cx<float>* gv) {
+  const h2_t z2 = {(_Float16)0.f, (_Float16)0.f};
+  const f4_t z4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const h4_t B0 = h4_of(h[k * 3], h[k * 3 + 1]), B1 = h4_of(h[k * 3 + 2], z2);
+    f4_t t = __builtin_amdgcn_mfma_f32_4x4x4f16(A00, B0, z4, 0, 0, 0);
+    t = __builtin_amdgcn_mfma_f32_4x4x4f16(A01, B1, t, 0, 0, 0);
+    f4_t b = __builtin_amdgcn_mfma_f32_4x4x4f16(A10, B0, z4, 0, 0, 0);
+    b = __builtin_amdgcn_mfma_f32_4x4x4f16(A11, B1, b, 0, 0, 0);
+    gv[k * 3] = {t[0], t[1]};
+    gv[k * 3 + 1] = {t[2], t[3]};
+    gv[k * 3 + 2] = {b[0], b[1]};
+  }
+}
+
 // one CG scalar step for right-hand side r from the reduced sum
 static __device__ void finalize_step(int mode, double sum, const CgState& S, int r, double* out) {
   if (mode == FIN_NORM) {

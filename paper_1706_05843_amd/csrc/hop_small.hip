@@ -1,4 +1,4 @@
-// The hop kernel for launches of few waves (FP64 and FP32; see hop_is_small).
+// The hop kernel for launches of few waves (see hop_is_small).
 //
 // On a small lattice the general kernel (kernels.hip: one lane per 5D site) is
 // one pass of a few waves over its 10 to 22 KB of straight-line code; most SIMDs
@@ -9,7 +9,9 @@
 // spin projection, one SU(3) product) and leaves its half spinor in LDS; then
 // six of them take one component pair each (the pairs q of the packed layout)
 // through the sum over the directions, the epilogue along s and the update,
-// since M_ee, D~ and their inverses act on every component alike.
+// since M_ee, D~ and their inverses act on every component alike. In FP16S the
+// six then meet once more for the site's scale. A CG iteration at 8^4 x 8, one
+// system: FP64 65 -> 39 us, FP32 52 -> 30, FP16S 48 -> 29.
 #include <hip/hip_runtime.h>
 
 #include "device_common.h"
@@ -118,6 +120,81 @@ __device__ __forceinline__ void project_mu(const cx<R>* v, R sg, cx<R>* h) {
   }
 }
 
+// FP16S: the arithmetic of the general kernel (packed halves up to the SU(3)
+// product, which sums in FP32), one direction per wave.
+template <int MU>
+__device__ __forceinline__ void project_h(const h2_t* x, bool neg, h2_t* h) {
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const h2_t u0 = x[c], u1 = x[3 + c], l0 = x[6 + c], l1 = x[9 + c];
+    const h2_t il0 = {-l0.y, l0.x}, il1 = {-l1.y, l1.x};
+    if constexpr (MU == 0) {
+      h[c] = neg ? u0 + il1 : u0 - il1;
+      h[3 + c] = neg ? u1 + il0 : u1 - il0;
+    } else if constexpr (MU == 1) {
+      h[c] = neg ? u0 + l1 : u0 - l1;
+      h[3 + c] = neg ? u1 - l0 : u1 + l0;
+    } else if constexpr (MU == 2) {
+      h[c] = neg ? u0 + il0 : u0 - il0;
+      h[3 + c] = neg ? u1 - il1 : u1 + il1;
+    } else {
+      h[c] = neg ? u0 - l0 : u0 + l0;
+      h[3 + c] = neg ? u1 - l1 : u1 + l1;
+    }
+  }
+}
+
+// the words (Re u, -Im u) and (Im u, Re u) of a half link element
+__device__ __forceinline__ unsigned re_word(unsigned w) { return w ^ 0x80000000u; }
+__device__ __forceinline__ unsigned im_word(unsigned w) { return (w >> 16) | (w << 16); }
+
+// gv = U h for both half spinors; U: the lane's 9 link words. Ls a multiple of 4
+// (mf): the four lanes of a block share the link, on the matrix cores with the
+// operands of the general kernel's product; else dot products.
+__device__ __forceinline__ void su3_half(const unsigned* U, bool mf, int lane, const h2_t* h, cx<float>* gv) {
+  if (mf) {
+    const bool second = (lane & 2) != 0, im = (lane & 1) != 0;
+    unsigned t[3], b[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const unsigned ut = second ? U[3 + k] : U[k], ub = U[6 + k];
+      t[k] = im ? im_word(ut) : re_word(ut);
+      b[k] = im ? im_word(ub) : re_word(ub);
+    }
+    su3_mfma_rows(h4_of(t[0], t[1]), h4_of(t[2], t[1]), h4_of(b[0], b[1]), h4_of(b[2], b[1]), h, gv);
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      float re = 0.f, im = 0.f;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const unsigned u = U[c * 3 + j];
+        re = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2_t, re_word(u)), h[k * 3 + j], re, false);
+        im = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2_t, im_word(u)), h[k * 3 + j], im, false);
+      }
+      gv[k * 3 + c] = {re, im};
+    }
+}
+
+// the two half words and the site scale of pair q
+struct Pair16 {
+  uint2 w;
+  float sc;
+};
+__device__ __forceinline__ size_t pair16_idx(const FD& f, int r, int q, int s, int i) {
+  return 2 * qidx16(f, r, q >> 1, s, i) + (q & 1);  // in units of 8 bytes
+}
+__device__ __forceinline__ Pair16 ld_pair16(const void* base, const FD& f, int r, int q, int s, int i) {
+  return {((const uint2*)base)[pair16_idx(f, r, q, s, i)], scale_ptr(base, f)[sidx(f, r, s, i)]};
+}
+__device__ __forceinline__ cx<float> half_cx(unsigned w) {
+  const h2_t h = __builtin_bit_cast(h2_t, w);
+  return {(float)h.x, (float)h.y};
+}
+
 template <int P, int ROLE>
 __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
   using RT = RoleT<ROLE>;
@@ -126,6 +203,7 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   cx<R>* s_g = (cx<R>*)smem;  // [direction][component of the half spinor][lane]
   __shared__ double s_red[SMW];
+  __shared__ float s_max[P == P16 ? 6 * 64 : 1];
   __shared__ int s_halt;
 
   const int Ls = a.Ls, Vh = a.Vh, G = 64 / Ls;
@@ -150,18 +228,37 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
     s_halt = __hip_atomic_load(a.halt + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int site = min(kk, Vh - 1);  // checkerboard order: a table lookup less in front of the gather
   const int n = a.nbr[(size_t)site * 8 + wave];
-  cx<R> U[9];
-#pragma unroll
-  for (int j = 0; j < 9; ++j) U[j] = ld_link<P>(a.links, ((size_t)site * 8 + wave) * 9 + j);
-  cx<R> v[12];
-  ld_spinor<P>(a.in, fd, r, s, n, v);
-  // this wave's pair of the same-site fields, needed after the sum
+  // the link and the neighbour, and this wave's pair of the same-site fields,
+  // needed after the sum
   const int q = wave;
   const size_t e = eidx(fd, r, q < 6 ? q : 0, s, site);
-  cx<R> y[2], z[2];
-  if (RT::BM != B_NONE && q < 6) ld_pair<P>(a.y, e, y[0], y[1]);
-  if (RT::OM == O_ADDZ && q < 6) ld_pair<P>(a.z, e, z[0], z[1]);
-  if (RT::OM == O_RUPD && q < 6) ld_pair<P>(a.r, e, z[0], z[1]);
+  cx<R> U[P == P16 ? 1 : 9], v[P == P16 ? 1 : 12], y[2], z[2];
+  unsigned Uh[P == P16 ? 9 : 1], vh[P == P16 ? 12 : 1];
+  float vsc = 0.f, zsc = 1.f;
+  if constexpr (P == P16) {
+#pragma unroll
+    for (int j = 0; j < 9; ++j) Uh[j] = ((const unsigned*)a.links)[((size_t)site * 8 + wave) * 9 + j];
+    vsc = scale_ptr(a.in, fd)[sidx(fd, r, s, n)];
+    ld_words16(a.in, fd, r, s, n, vh);
+    if (RT::BM != B_NONE && q < 6) {
+      const Pair16 t = ld_pair16(a.y, fd, r, q, s, site);
+      y[0] = t.sc * half_cx(t.w.x);
+      y[1] = t.sc * half_cx(t.w.y);
+    }
+    if ((RT::OM == O_ADDZ || RT::OM == O_RUPD) && q < 6) {
+      const Pair16 t = ld_pair16(RT::OM == O_ADDZ ? a.z : a.r, fd, r, q, s, site);
+      z[0] = half_cx(t.w.x);
+      z[1] = half_cx(t.w.y);
+      zsc = t.sc;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 9; ++j) U[j] = ld_link<P>(a.links, ((size_t)site * 8 + wave) * 9 + j);
+    ld_spinor<P>(a.in, fd, r, s, n, v);
+    if (RT::BM != B_NONE && q < 6) ld_pair<P>(a.y, e, y[0], y[1]);
+    if (RT::OM == O_ADDZ && q < 6) ld_pair<P>(a.z, e, z[0], z[1]);
+    if (RT::OM == O_RUPD && q < 6) ld_pair<P>(a.r, e, z[0], z[1]);
+  }
   const R m = (R)a.mop[r], cpd = (R)a.cpd, cmd = (R)a.cmd, qd = cmd * recip(cpd);
   const double* sc = a.scoef + (size_t)r * (SCOEF_HEAD + 2 * Ls);
   const R sk0 = (R)sc[1], us = (R)sc[SCOEF_HEAD + s], a_s = (R)sc[SCOEF_HEAD + Ls + s];
@@ -178,15 +275,46 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
   }
 
   // direction `wave`: (D~ in)/(c+d) of the neighbour, projected, times the link
-  if constexpr (RT::PRE) {
+  const R sg = ((wave < 4) != RT::DAG) ? R(-1) : R(1);
+  if constexpr (P == P16) {
+    // the premix in units of the largest of the three site scales involved
+    h2_t x[12], h[6];
+    float unit = vsc;
+    if constexpr (RT::PRE) {
+      const float qx = (float)(a.cmd / a.cpd);
+      const float su = __shfl(vsc, col.dn, 64) * (col.fdn * qx), sl = __shfl(vsc, col.up, 64) * (col.fup * qx);
+      unit = fmaxf(vsc, fmaxf(fabsf(su), fabsf(sl)));
+      unit = unit > 0.f ? unit : 1.f;
+      const float inv = recip(unit);
+      const _Float16 f0 = (_Float16)(vsc * inv), fu = (_Float16)(su * inv), fl = (_Float16)(sl * inv);
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-      const cx<R> t = shfl2(v[c], c < 6 ? col.dn : col.up);
-      v[c] = cfma_r((c < 6 ? col.fdn : col.fup) * qd, t, v[c]);
+      for (int c = 0; c < 12; ++c) {
+        const unsigned t = __shfl(vh[c], c < 6 ? col.dn : col.up, 64);
+        x[c] = (c < 6 ? fu : fl) * __builtin_bit_cast(h2_t, t) + f0 * __builtin_bit_cast(h2_t, vh[c]);
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < 12; ++c) x[c] = __builtin_bit_cast(h2_t, vh[c]);
     }
-  }
-  {
-    const R sg = ((wave < 4) != RT::DAG) ? R(-1) : R(1);
+    const bool neg = sg < R(0);
+    switch (wave & 3) {
+      case 0: project_h<0>(x, neg, h); break;
+      case 1: project_h<1>(x, neg, h); break;
+      case 2: project_h<2>(x, neg, h); break;
+      default: project_h<3>(x, neg, h); break;
+    }
+    cx<float> gv[6];
+    su3_half(Uh, Ls % 4 == 0, lane, h, gv);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) s_g[(wave * 6 + c) * 64 + lane] = unit * gv[c];
+  } else {
+    if constexpr (RT::PRE) {
+#pragma unroll
+      for (int c = 0; c < 12; ++c) {
+        const cx<R> t = shfl2(v[c], c < 6 ? col.dn : col.up);
+        v[c] = cfma_r((c < 6 ? col.fdn : col.fup) * qd, t, v[c]);
+      }
+    }
     cx<R> h[6];
     switch (wave & 3) {
       case 0: project_mu<0>(v, sg, h); break;
@@ -207,9 +335,9 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
   __syncthreads();
 
   double nrm = 0.0;
+  cx<R> w[2];
   if (q < 6) {
     // the pair's components of sum over directions [g ; sg A^dag g]
-    cx<R> w[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int c = 2 * q + t, spin = c / 3, cc = c - 3 * spin;
@@ -304,18 +432,42 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
         }
       }
     }
-    if (live) {
-      if constexpr (RT::OM == O_ADDZ) {
+    if constexpr (RT::OM == O_ADDZ) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t) w[t] = z[t] - w[t];
-      } else if constexpr (RT::OM == O_RUPD) {  // w carries -alpha
+      for (int t = 0; t < 2; ++t) w[t] = (P == P16 ? (R)zsc * z[t] : z[t]) - w[t];
+    } else if constexpr (RT::OM == O_RUPD) {  // w carries -alpha
 #pragma unroll
-        for (int t = 0; t < 2; ++t) w[t] = z[t] + w[t];
-      }
+      for (int t = 0; t < 2; ++t) w[t] = P == P16 ? cfma_r((R)zsc, z[t], w[t]) : z[t] + w[t];
+    }
+    if constexpr (P == P16) {
+      s_max[q * 64 + lane] = fmaxf(fmaxf(fabsf(w[0].r), fabsf(w[0].i)), fmaxf(fabsf(w[1].r), fabsf(w[1].i)));
+    } else if (live) {
       st_pair<P>(RT::OM == O_RUPD || RT::OM == O_STORE_R ? a.r : a.out, e, w[0], w[1]);
       if constexpr (RT::NRM)
 #pragma unroll
         for (int t = 0; t < 2; ++t) nrm += (double)w[t].r * w[t].r + (double)w[t].i * w[t].i;
+    }
+  }
+  if constexpr (P == P16) {  // the encoding, and |v|^2 from it, as st_spinor16
+    __syncthreads();
+    if (q < 6 && live) {
+      float mx = 0.f;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) mx = fmaxf(mx, s_max[k * 64 + lane]);
+      const float inv = mx > 0.f ? recip(mx) : 0.f;
+      unsigned hw[2];
+      float ns = 0.f;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const float xr = (float)w[t].r * inv, xi = (float)w[t].i * inv;
+        ns = fma(xi, xi, fma(xr, xr, ns));
+        const h2_t h = {(_Float16)xr, (_Float16)xi};
+        hw[t] = __builtin_bit_cast(unsigned, h);
+      }
+      void* dst = RT::OM == O_RUPD || RT::OM == O_STORE_R ? a.r : a.out;
+      ((uint2*)dst)[pair16_idx(fd, r, q, s, site)] = make_uint2(hw[0], hw[1]);
+      if (q == 0) ((float*)scale_ptr(dst, fd))[sidx(fd, r, s, site)] = mx;
+      if constexpr (RT::NRM) nrm = (double)mx * (double)mx * (double)ns;
     }
   }
   if constexpr (RT::NRM) {
@@ -372,7 +524,11 @@ int launch_small_p(int role, const HopArgs& a, hipStream_t st) {
 }  // namespace
 
 int launch_hop_small(int prec, int role, const HopArgs& a, hipStream_t st) {
-  return prec == P64 ? launch_small_p<P64>(role, a, st) : launch_small_p<P32>(role, a, st);
+  switch (prec) {
+    case P64: return launch_small_p<P64>(role, a, st);
+    case P32: return launch_small_p<P32>(role, a, st);
+  }
+  return launch_small_p<P16>(role, a, st);
 }
 
 }  // namespace eofa

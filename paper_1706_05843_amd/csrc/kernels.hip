@@ -175,12 +175,8 @@ constexpr int kOcc16 = 5;
 // its own U h. Per half spinor: top rows (Re, Im of colours 0, 1) and bottom
 // rows (colour 2, its two rows repeated on lanes 2, 3 of the block), each
 // over the K blocks (colours 0, 1) and (colour 2, zero): four products, in
-// place of 18 v_dot2 on the vector ALU. Same FP16 products, FP32 sums.
-typedef _Float16 h4_t __attribute__((ext_vector_type(4)));
-typedef float f4_t __attribute__((ext_vector_type(4)));
-typedef unsigned u2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ h4_t h4_of(unsigned lo, unsigned hi) { return __builtin_bit_cast(h4_t, u2_t{lo, hi}); }
-__device__ __forceinline__ h4_t h4_of(h2_t lo, h2_t hi) { return __builtin_shufflevector(lo, hi, 0, 1, 2, 3); }
+// place of 18 v_dot2 on the vector ALU (su3_mfma_rows). Same FP16 products,
+// FP32 sums.
 
 // g = U h for the two projected half spinors h[0..2], h[3..5] of one
 // direction on the matrix cores. Uw: the direction's 9 staged entries (entry
@@ -192,21 +188,7 @@ __device__ __forceinline__ h4_t h4_of(h2_t lo, h2_t hi) { return __builtin_shuff
 __device__ __forceinline__ void su3_mfma(const unsigned* Uw, int top, int bot, const h2_t* h, cx<float>* gv) {
   const unsigned* Ut = Uw + top;
   const unsigned* Ub = Uw + bot;
-  const h4_t A00 = h4_of(Ut[0], Ut[2]), A01 = h4_of(Ut[4], Ut[2]);
-  const h4_t A10 = h4_of(Ub[12], Ub[14]), A11 = h4_of(Ub[16], Ub[14]);
-  const h2_t z2 = {(_Float16)0.f, (_Float16)0.f};
-  const f4_t z4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const h4_t B0 = h4_of(h[k * 3], h[k * 3 + 1]), B1 = h4_of(h[k * 3 + 2], z2);
-    f4_t t = __builtin_amdgcn_mfma_f32_4x4x4f16(A00, B0, z4, 0, 0, 0);
-    t = __builtin_amdgcn_mfma_f32_4x4x4f16(A01, B1, t, 0, 0, 0);
-    f4_t b = __builtin_amdgcn_mfma_f32_4x4x4f16(A10, B0, z4, 0, 0, 0);
-    b = __builtin_amdgcn_mfma_f32_4x4x4f16(A11, B1, b, 0, 0, 0);
-    gv[k * 3] = {t[0], t[1]};
-    gv[k * 3 + 1] = {t[2], t[3]};
-    gv[k * 3 + 2] = {b[0], b[1]};
-  }
+  su3_mfma_rows(h4_of(Ut[0], Ut[2]), h4_of(Ut[4], Ut[2]), h4_of(Ub[12], Ub[14]), h4_of(Ub[16], Ub[14]), h, gv);
 }
 
 // the same products as v_dot2 on the vector ALU (any Ls); U: the direction's
@@ -1278,13 +1260,14 @@ constexpr int acc_prec() {
 
 // Launches whose tiles of one wave leave most of the chip idle go to the kernel
 // of hop_small.hip, which shares each tile among eight waves. Time per FP64 /
-// FP32 CG iteration there and here (us): 16 tiles (4^4, Ls = 8) 32 and 57 / 27
-// and 47; 256 (8^4) 39 and 65 / 30 and 52; 512 51 and 74 / 35 and 57; 820 (Ls =
-// 12) 86 and 89 / 53 and 64; 1024 91 and 98 / 52 and 70; 2048 167 and 144 / 86
-// and 88, at Ls = 16, whose row form here is faster, 180 and 129 / 93 and 71.
-// The single hop in FP64 is level at 820.
+// FP32 / FP16S CG iteration there and here (us): 16 tiles (4^4, Ls = 8) 32 and 57
+// / 27 and 47 / 27 and 45; 256 (8^4) 39 and 65 / 30 and 52 / 29 and 48; 512 51 and
+// 74 / 35 and 57 / 34 and 50; 820 (Ls = 12) 86 and 89 / 53 and 64 / 46 and 56; 1024
+// 91 and 98 / 52 and 70 / 46 and 60; 2048 167 and 144 / 86 and 88 / 72 and 72. At
+// Ls = 16, whose row form here is faster, FP16S 29 and 35 at 32 tiles, 38 and 40 at 512,
+// and at 2048 180 and 129 / 93 and 71 / 79 and 55. The single hop in FP64 is level
+// at 820.
 bool hop_is_small(int prec, int Vh, int Ls, int nrhs) {
-  if (prec == P16) return false;
   const size_t G = sites_per_wave(Ls), tiles = ((size_t)Vh + G - 1) / G;
   return tiles * nrhs <= (prec == P64 ? 640u : 1024u) / (Ls == 16 ? 2 : 1);
 }

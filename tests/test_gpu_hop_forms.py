@@ -74,3 +74,42 @@ def test_fixed_iterations(Ls, prec, tol, form):
         _, st = ctx.eofa_cg_solve(systems[r:r + 1], f[r:r + 1].contiguous(), one, prm)
         assert np.isfinite(st[0]["true_resid"])
         assert rel(psi[r], one[0]) < tol, r
+
+
+# FP16S: both forms take the same halves through the same products and differ in
+# the order of the FP32 sums alone, which now and then rounds a stored half the
+# other way: by 2^-11 of the site's largest value at most, in each of the two
+# parts, in few components. Iterations: such a step in each of the ten.
+@pytest.mark.parametrize("Ls", [2, 6, 8, 12, 16, 20, 32])
+def test_dslash_fp16s(Ls):
+    ctx, systems, f, n = setup(Ls)
+    prec = eofa.FP16S
+    for dag in (0, 1):
+        pin, pout = ctx.new_packed(prec, n), ctx.new_packed(prec, n)
+        ctx.eofa_pack(f, pin, 1, prec, nrhs=n)
+        ctx.eofa_dslash(systems, pin, pout, 0, dag, prec, nrhs=n)
+        out = torch.zeros_like(f)
+        ctx.eofa_unpack(pout, out, 0, prec, nrhs=n)
+        for r in (0, 1, 2, n - 1):
+            one, two = ctx.new_packed(prec), ctx.new_packed(prec)
+            ctx.eofa_pack(f[r:r + 1].contiguous(), one, 1, prec)
+            ctx.eofa_dslash(systems[r:r + 1], one, two, 0, dag, prec)
+            ref = torch.zeros_like(f[:1])
+            ctx.eofa_unpack(two, ref, 0, prec)
+            assert rel(out[r], ref[0]) < 2 ** -10.5 + 2e-6, (dag, r)
+            far = (out[r] - ref[0]).abs() > 2e-6 * ref.abs().max()
+            assert float(far.float().mean()) < 0.01, (dag, r)
+
+
+@pytest.mark.parametrize("Ls", [2, 6, 8, 12, 16, 20, 32])
+@pytest.mark.parametrize("form", [0, 1])
+def test_fixed_iterations_fp16s(Ls, form):
+    ctx, systems, f, n = setup(Ls)
+    prm = eofa.make_params(fixed_iters=10, inner_prec=eofa.FP16S, form=form)
+    psi = torch.zeros_like(f)
+    ctx.eofa_cg_solve(systems, f, psi, prm)
+    for r in (0, 1, 2, n - 1):
+        one = torch.zeros_like(f[:1])
+        _, st = ctx.eofa_cg_solve(systems[r:r + 1], f[r:r + 1].contiguous(), one, prm)
+        assert np.isfinite(st[0]["true_resid"])
+        assert rel(psi[r], one[0]) < 10 * 2 ** -11, r
