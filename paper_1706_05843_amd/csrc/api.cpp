@@ -245,13 +245,15 @@ HopArgs base_args(eofa_ctx* C, int prec, int out_parity, int nrhs) {
   a.Ls = C->g.Ls;
   a.nrhs = nrhs;
   // right-hand sides per work-group where the autotuner has not chosen: all of
-  // them share the staged links; but in FP64 and FP32, when one field's input and
-  // output exceed the 256 MB MALL, a long loop over right-hand sides drifts the
-  // work-groups of an XCD apart and its L2 loses the columns they share. Dslash,
-  // 24^3 x 64 x 12, by right-hand sides per work-group: 12 x FP32 1: 4839 us,
-  // 2: 4612, 3: 4675, 12: 5030; 3 x FP64 2: 2688, 3: 2779; 4 x FP16S 2: 902,
-  // 4: 887; within the MALL (16^3 x 32 x 16, 4 x FP32) 2: 305, 4: 305.
-  a.rhs_block = prec != P16 && 2 * packed_bytes(prec, C->g, 1) > (size_t(256) << 20) ? std::min(nrhs, 2) : nrhs;
+  // them share the staged links; but in FP64 and FP32, when input and output of all
+  // of them exceed the 256 MB MALL, a long loop over right-hand sides drifts the
+  // work-groups of an XCD apart and its L2 loses the columns they share. Dslash by
+  // right-hand sides per work-group: 24^3 x 64 x 12, 12 x FP32 1: 4839 us, 2: 4612,
+  // 3: 4675, 12: 5030; 3 x FP64 2: 2688, 3: 2779; 4 x FP16S 2: 902, 4: 887; with
+  // streamed output, 24.14.20.8 x 12, 6 x FP32 2: 129, 6: 145; 4 x FP64 2: 205, 4:
+  // 215; 16^3 x 32 x 16, 4 x FP32 2: 285, 4: 294; within the MALL (12^3 x 24 x 8, 6 x
+  // FP32) 2: 74, 6: 75.
+  a.rhs_block = prec != P16 && 2 * packed_bytes(prec, C->g, nrhs) > (size_t(256) << 20) ? std::min(nrhs, 2) : nrhs;
   a.W = default_waves(C->g.Ls);
   auto it = C->tuned.find(prec * 4096 + nrhs);
   if (it != C->tuned.end()) {

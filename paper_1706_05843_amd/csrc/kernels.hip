@@ -1330,16 +1330,18 @@ size_t hop_lds_bytes(int prec, int role, int Ls, int W) {
 }
 
 // Whether a launch writes its output with non-temporal stores: when input and
-// output together exceed the 256 MB MALL the next kernel finds nothing of the
-// output on the chip, and the store only evicts neighbour spinors this kernel
-// still gathers from L2. One box: FP64 16^3 x 32 x 16 169 -> 153 us, FP64
-// 24^3 x 64 x 12 907 -> 862, FP32 411 -> 401, 12 x FP32 (two right-hand sides per
-// work-group) 4590 -> 4426. FP16S stays with plain stores: level beyond the MALL,
-// 5 % slower on the 16^3 x 32 x 16 solve, whose next kernel reads the output
-// there.
+// output of all right-hand sides together exceed the 256 MB MALL the next kernel
+// finds little of the output on the chip, and the store only evicts neighbour
+// spinors this kernel still gathers from L2. One box: FP64 16^3 x 32 x 16 169 ->
+// 153 us, FP64 24^3 x 64 x 12 907 -> 862, FP32 411 -> 401, 12 x FP32 4590 -> 4426;
+// where one right-hand side would fit: 24.14.20.8 x 12 4 x FP64 241 -> 215, 6 x
+// FP32 164 -> 145, 16^3 x 32 x 8 3 x FP64 279 -> 259, and batched CG iterations
+// there (2 x FP64) 1075 -> 1039 us; below (6 x FP32 on 12^3 x 24 x 8, 191 MB)
+// level. FP16S stays with plain stores: level beyond the MALL, 5 % slower on the
+// 16^3 x 32 x 16 solve, whose next kernel reads the output there.
 bool stream_output(int prec, const HopArgs& a) {
   const size_t site = prec == P64 ? 192 : 96;
-  return prec != P16 && 2 * site * a.Vh * a.Ls > (size_t(256) << 20);
+  return prec != P16 && 2 * site * a.Vh * a.Ls * a.nrhs > (size_t(256) << 20);
 }
 
 template <int P, int ROLE>

@@ -53,3 +53,29 @@ def test_every_site_written_and_sampled(big, prec, dag, tol):
         if sum(x) % 2 == 0:
             ref = f(act, U, m, ph, x)
             assert np.abs(got[:, x[3], x[2], x[1], x[0]] - ref).max() < tol * np.abs(ref).max(), x
+
+
+@pytest.mark.parametrize("prec,n", [(eofa.FP64, 3), (eofa.FP64, 4), (eofa.FP32, 5)])
+def test_right_hand_sides_beyond_the_mall_together(prec, n):
+    """Fields that fit the MALL one by one and exceed it together (streamed output,
+    two right-hand sides per work-group, an odd one left over): the same bits as
+    one launch each."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dims, Ls = (18, 14, 20, 12), 12
+    ctx = eofa.Context(eofa.make_action(dims, Ls, M5, B5, C5),
+                       torch.from_numpy(synth.gauge_field(dims, 0.5, seed=1012)).cuda())
+    one = ctx.packed_bytes(prec, 1)
+    assert 2 * one < 256 << 20 < 2 * n * one
+    f = synth.fermion_torch(dims, Ls, seed=2012, nrhs=n)
+    systems = [(0.02 + 0.01 * r, 0.0, 0.0, 0.0, 1) for r in range(n)]
+    pin, pout = ctx.new_packed(prec, n), ctx.new_packed(prec, n)
+    ctx.eofa_pack(f, pin, 1, prec, nrhs=n)
+    for dag in (0, 1):
+        pout.fill_(255)
+        ctx.eofa_dslash(systems, pin, pout, 0, dag, prec, nrhs=n)
+        for r in range(n):
+            ref = ctx.new_packed(prec)
+            ctx.eofa_dslash(systems[r:r + 1], pin[r * one:(r + 1) * one], ref, 0, dag, prec)
+            assert torch.equal(pout[r * one:(r + 1) * one], ref), (dag, r)
+    ctx.close()
