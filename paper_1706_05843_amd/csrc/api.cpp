@@ -245,15 +245,26 @@ HopArgs base_args(eofa_ctx* C, int prec, int out_parity, int nrhs) {
   a.Ls = C->g.Ls;
   a.nrhs = nrhs;
   // right-hand sides per work-group where the autotuner has not chosen: all of
-  // them share the staged links; but in FP64 and FP32, when input and output of all
-  // of them exceed the 256 MB MALL, a long loop over right-hand sides drifts the
-  // work-groups of an XCD apart and its L2 loses the columns they share. Dslash by
-  // right-hand sides per work-group: 24^3 x 64 x 12, 12 x FP32 1: 4839 us, 2: 4612,
-  // 3: 4675, 12: 5030; 3 x FP64 2: 2688, 3: 2779; 4 x FP16S 2: 902, 4: 887; with
-  // streamed output, 24.14.20.8 x 12, 6 x FP32 2: 129, 6: 145; 4 x FP64 2: 205, 4:
-  // 215; 16^3 x 32 x 16, 4 x FP32 2: 285, 4: 294; within the MALL (12^3 x 24 x 8, 6 x
-  // FP32) 2: 74, 6: 75.
-  a.rhs_block = prec != P16 && 2 * packed_bytes(prec, C->g, nrhs) > (size_t(256) << 20) ? std::min(nrhs, 2) : nrhs;
+  // them share the staged links, except where
+  // * input and output of all of them exceed the 256 MB MALL (FP64, FP32): a long
+  //   loop over right-hand sides drifts the work-groups of an XCD apart and its L2
+  //   loses the columns they share. Dslash by right-hand sides per work-group:
+  //   24^3 x 64 x 12, 12 x FP32 1: 4839 us, 2: 4612, 3: 4675, 12: 5030; 3 x FP64 2:
+  //   2688, 3: 2779; 4 x FP16S 2: 902, 4: 887; with streamed output, 24.14.20.8 x 12,
+  //   6 x FP32 2: 129, 6: 145; 4 x FP64 2: 205, 4: 215; 16^3 x 32 x 16, 4 x FP32 2:
+  //   285, 4: 294; within the MALL (12^3 x 24 x 8, 6 x FP32) 2: 74, 6: 75;
+  // * one right-hand side has too few waves for the 1024 SIMDs, which then wait
+  //   for the loop: 6.6.8.12 x 12 (345 waves), 12 x FP16S 1: 18, 12: 50; 768 waves,
+  //   four right-hand sides, FP64 / FP32 / FP16S 1: 36 / 20 / 15, 4: 48 / 30 / 24;
+  //   1024 46 / 23 / 18 and 49 / 31 / 26; 1280 56 / 27 / 21 and 54 / 33 / 27; 1536
+  //   63 / 32 / 22 and 60 / 34 / 27; 2048 84 / 41 / 28 and 74 / 39 / 29.
+  const size_t waves = ((size_t)C->g.Vh + 64 / C->g.Ls - 1) / (64 / C->g.Ls);
+  if (waves <= (prec == P64 ? 1024u : 1536u))
+    a.rhs_block = 1;
+  else if (prec != P16 && 2 * packed_bytes(prec, C->g, nrhs) > (size_t(256) << 20))
+    a.rhs_block = std::min(nrhs, 2);
+  else
+    a.rhs_block = nrhs;
   a.W = default_waves(C->g.Ls);
   auto it = C->tuned.find(prec * 4096 + nrhs);
   if (it != C->tuned.end()) {
