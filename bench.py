@@ -92,7 +92,7 @@ def cpu_info():
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("kernels.hip", "internal.h"):
+    for f in ("kernels.hip", "hop_common.h", "internal.h"):
         h.update(open(os.path.join(ROOT, "paper_1706_05843_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
