@@ -252,7 +252,7 @@ int build_fifth(const Geometry& g, double M5, double b5, double c5, const eofa_s
 // large lattices, so the t neighbours come from HBM again. There (kSweep 5D
 // sites of a parity and more) the blocks are dealt out slab by slab: every XCD
 // takes an eighth of each bt-thick t slab and all sweep t together, sharing one
-// window. Measured, one box, 24^3 x 64, Ls = 12, plain order against this one:
+// window. Measured, one card, 24^3 x 64, Ls = 12, plain order against this one:
 // FP64 958 -> 907 us, FP32 436 -> 416, FP16S 273 -> 260; at 16^3 x 32, Ls = 16
 // (1.05 M sites, fields within the MALL) it is level, and at 8 x 12 x 6 x 16,
 // Ls = 8 it costs 7 %: each XCD's eighth of a slab is then a few rows, most of

@@ -1332,7 +1332,7 @@ size_t hop_lds_bytes(int prec, int role, int Ls, int W) {
 // Whether a launch writes its output with non-temporal stores: when input and
 // output of all right-hand sides together exceed the 256 MB MALL the next kernel
 // finds little of the output on the chip, and the store only evicts neighbour
-// spinors this kernel still gathers from L2. One box: FP64 16^3 x 32 x 16 169 ->
+// spinors this kernel still gathers from L2. One card: FP64 16^3 x 32 x 16 169 ->
 // 153 us, FP64 24^3 x 64 x 12 907 -> 862, FP32 411 -> 401, 12 x FP32 4590 -> 4426;
 // where one right-hand side would fit: 24.14.20.8 x 12 4 x FP64 241 -> 215, 6 x
 // FP32 164 -> 145, 16^3 x 32 x 8 3 x FP64 279 -> 259, and batched CG iterations
