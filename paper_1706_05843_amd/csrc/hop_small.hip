@@ -274,14 +274,15 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
     if (s_halt != 0) return;
   }
 
-  // direction `wave`: (D~ in)/(c+d) of the neighbour, projected, times the link
+  // direction `wave`: (D~ in)/(c+d) of the neighbour, projected, times the link;
+  // the premix factor rounds once, from FP64 (cmd * recip(cpd) in R is up to 2 ulp off)
   const R sg = ((wave < 4) != RT::DAG) ? R(-1) : R(1);
+  const R qx = (R)(a.cmd / a.cpd);
   if constexpr (P == P16) {
     // the premix in units of the largest of the three site scales involved
     h2_t x[12], h[6];
     float unit = vsc;
     if constexpr (RT::PRE) {
-      const float qx = (float)(a.cmd / a.cpd);
       const float su = __shfl(vsc, col.dn, 64) * (col.fdn * qx), sl = __shfl(vsc, col.up, 64) * (col.fup * qx);
       unit = fmaxf(vsc, fmaxf(fabsf(su), fabsf(sl)));
       unit = unit > 0.f ? unit : 1.f;
@@ -312,7 +313,7 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
 #pragma unroll
       for (int c = 0; c < 12; ++c) {
         const cx<R> t = shfl2(v[c], c < 6 ? col.dn : col.up);
-        v[c] = cfma_r((c < 6 ? col.fdn : col.fup) * qd, t, v[c]);
+        v[c] = cfma_r((c < 6 ? col.fdn : col.fup) * qx, t, v[c]);
       }
     }
     cx<R> h[6];

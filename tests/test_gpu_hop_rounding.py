@@ -1,0 +1,59 @@
+"""The eight-wave form of the hop (hop_small.hip) rounds where the general form
+(kernels.hip) does. One system takes the first, the same system batched until
+the tiles exceed its range the second.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1706_05843_amd import eofa, synth
+
+pytestmark = pytest.mark.gpu
+
+M5 = 1.8
+DIMS = (4, 4, 4, 4)
+
+
+def context(Ls, U, b5=1.5):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return eofa.Context(eofa.make_action(DIMS, Ls, M5, b5, b5 - 1.0), torch.from_numpy(U).cuda())
+
+
+def batch(Ls):
+    """Right-hand sides that take the general form: more than 1024 tiles in all."""
+    g = 64 // Ls
+    tiles = (int(np.prod(DIMS)) // 2 + g - 1) // g
+    return 1024 // tiles + 1
+
+
+def both_forms(ctx, f, prec, dag, m=0.03):
+    """Dslash of f alone and as the first of a batch: canonical fields."""
+    n = batch(ctx.Ls)
+    out = []
+    for k in (1, n):
+        pin, pout = ctx.new_packed(prec, k), ctx.new_packed(prec, k)
+        ctx.eofa_pack(f.expand((k,) + f.shape[1:]).contiguous(), pin, 1, prec, nrhs=k)
+        ctx.eofa_dslash([(m, 0.0, 0.0, 0.0, 1)] * k, pin, pout, 0, dag, prec, nrhs=k)
+        full = torch.zeros((k,) + f.shape[1:], dtype=f.dtype, device="cuda")
+        ctx.eofa_unpack(pout, full, 0, prec, nrhs=k)
+        out.append(full[0])
+    return out
+
+
+# One component of one 5D site on unit links: every output is that component
+# times the premix factor (c-d)/(c+d) (or 1, or -m times it across the wrap)
+# times the leading factor, all other terms exact zeros, so the forms agree to
+# the bit if each forms the two factors alike.
+@pytest.mark.parametrize("b5", [1.5, 1.6, 1.7, 1.8, 1.95, 2.3])
+@pytest.mark.parametrize("prec", [eofa.FP64, eofa.FP32])
+@pytest.mark.parametrize("Ls", [8, 12, 16])
+def test_premix_factor(Ls, prec, b5):
+    ctx = context(Ls, synth.unit_gauge(DIMS), b5)
+    for s, c in ((Ls // 2, 1), (Ls - 1, 4), (0, 9)):  # inside, and both wraps
+        f = torch.zeros((1, Ls) + DIMS[::-1] + (4, 3), dtype=torch.complex128, device="cuda")
+        f[0, s, 1, 2, 1, 1, c // 3, c % 3] = 1.0
+        small, general = both_forms(ctx, f, prec, 0)
+        assert int((general != 0).sum()) > 16
+        assert torch.equal(small, general), (s, c)
