@@ -204,6 +204,7 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
   cx<R>* s_g = (cx<R>*)smem;  // [direction][component of the half spinor][lane]
   __shared__ double s_red[SMW];
   __shared__ float s_max[P == P16 ? 6 * 64 : 1];
+  __shared__ float s_unit[P == P16 ? SMW * 64 : 1];  // FP16S: [direction][lane], the half spinors' unit
   __shared__ int s_halt;
 
   const int Ls = a.Ls, Vh = a.Vh, G = 64 / Ls;
@@ -307,7 +308,8 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
     cx<float> gv[6];
     su3_half(Uh, Ls % 4 == 0, lane, h, gv);
 #pragma unroll
-    for (int c = 0; c < 6; ++c) s_g[(wave * 6 + c) * 64 + lane] = unit * gv[c];
+    for (int c = 0; c < 6; ++c) s_g[(wave * 6 + c) * 64 + lane] = gv[c];
+    s_unit[wave * 64 + lane] = unit;
   } else {
     if constexpr (RT::PRE) {
 #pragma unroll
@@ -338,29 +340,6 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
   double nrm = 0.0;
   cx<R> w[2];
   if (q < 6) {
-    // the pair's components of sum over directions [g ; sg A^dag g]
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int c = 2 * q + t, spin = c / 3, cc = c - 3 * spin;
-      cx<R> acc = {R(0), R(0)};
-      if (spin < 2) {
-#pragma unroll
-        for (int d = 0; d < 8; ++d) acc = acc + s_g[(d * 6 + spin * 3 + cc) * 64 + lane];
-      } else {
-        const bool hi = spin == 3;
-#pragma unroll
-        for (int d = 0; d < 8; ++d) {
-          const int mu = d & 3;
-          const R sg = ((d < 4) != RT::DAG) ? R(-1) : R(1);
-          // A^dag g: mu 0 (i g1, i g0), 1 (g1, -g0), 2 (i g0, -i g1), 3 (g0, g1)
-          const int k = (mu < 2) != hi ? 1 : 0;
-          cx<R> u = s_g[(d * 6 + k * 3 + cc) * 64 + lane];
-          if (mu == 0 || mu == 2) u = mul_i(u);
-          acc = cfma_r((mu == 1 || mu == 2) && hi ? -sg : sg, u, acc);
-        }
-      }
-      w[t] = acc;
-    }
     // the leading factor: -1/2, the (c+d) of D~ on the input, and the
     // epilogue's sign, (c+d) and normalisation
     R fold = RT::PRE ? R(-0.5) * cpd : R(-0.5);
@@ -372,8 +351,39 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
     R vscale = R(1);
     if constexpr (RT::OM == O_RUPD) vscale = -(R)a.alpha[r];
     fold *= vscale;
+
+    // the pair's components of sum over directions [g ; sg A^dag g]; in FP16S each
+    // direction's unit times the leading factor scales its half spinor as it is added
+    R k[P == P16 ? 8 : 1];
+    if constexpr (P == P16)
 #pragma unroll
-    for (int t = 0; t < 2; ++t) w[t] = fold * w[t];
+      for (int d = 0; d < 8; ++d) k[d] = s_unit[d * 64 + lane] * fold;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int c = 2 * q + t, spin = c / 3, cc = c - 3 * spin;
+      cx<R> acc = {R(0), R(0)};
+      if (spin < 2) {
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+          const cx<R> u = s_g[(d * 6 + spin * 3 + cc) * 64 + lane];
+          acc = P == P16 ? cfma_r(k[P == P16 ? d : 0], u, acc) : acc + u;
+        }
+      } else {
+        const bool hi = spin == 3;
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+          const int mu = d & 3;
+          // A^dag g: mu 0 (i g1, i g0), 1 (g1, -g0), 2 (i g0, -i g1), 3 (g0, g1)
+          const bool neg = ((d < 4) != RT::DAG) != ((mu == 1 || mu == 2) && hi);
+          const int half = (mu < 2) != hi ? 1 : 0;
+          cx<R> u = s_g[(d * 6 + half * 3 + cc) * 64 + lane];
+          if (mu == 0 || mu == 2) u = mul_i(u);
+          const R f = P == P16 ? k[P == P16 ? d : 0] : R(1);
+          acc = cfma_r(neg ? -f : f, u, acc);
+        }
+      }
+      w[t] = P == P16 ? acc : fold * acc;
+    }
 
     const bool shifted = sk0 != R(0) && (chi > 0) == col.plus;  // the shift acts on this chirality
     const int star = col.plus ? Ls - 1 : 0, star_lane = g * Ls + star;

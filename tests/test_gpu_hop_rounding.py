@@ -57,3 +57,20 @@ def test_premix_factor(Ls, prec, b5):
         small, general = both_forms(ctx, f, prec, 0)
         assert int((general != 0).sum()) > 16
         assert torch.equal(small, general), (s, c)
+
+
+# One 5D site in FP16S: a single direction reaches each output site (extents of
+# 4), so the FP32 sum over the directions has one term, (unit times the leading
+# factor) times the product, rounded once in either form, and the encoding of it
+# is the same bits.
+@pytest.mark.parametrize("dag", [0, 1])
+@pytest.mark.parametrize("Ls", [6, 8, 10, 12, 16, 20, 24, 32])
+def test_half_spinors_fp16s(Ls, dag):
+    ctx = context(Ls, synth.gauge_field(DIMS, 0.5, 81))
+    x = synth.fermion(DIMS, Ls, 82)
+    for s in (0, Ls // 2, Ls - 1):
+        f = torch.zeros((1, Ls) + DIMS[::-1] + (4, 3), dtype=torch.complex128, device="cuda")
+        f[0, s, 1, 2, 1, 1] = torch.from_numpy(x[s, 1, 2, 1, 1]).cuda()
+        small, general = both_forms(ctx, f, eofa.FP16S, dag)
+        assert int((general != 0).sum()) > 64
+        assert torch.equal(small, general), s
