@@ -51,7 +51,8 @@ __device__ __forceinline__ void lacc2(cx<R>* z, const cx<R>* y, const SCol<R>& n
   }
 }
 
-// z <- sum_{k<Ls} (x L)^k z (TRANS: L^T), one pass per prime factor of Ls
+// z <- sum_{k<Ls} (x L)^k z (TRANS: L^T), one pass per prime factor of Ls, one
+// rounding per term
 template <class R, bool TRANS>
 __device__ __forceinline__ void series2(cx<R>* z, int s, int g, int Ls, R x, R m, bool plus) {
   const bool dn = plus != TRANS;
@@ -60,7 +61,7 @@ __device__ __forceinline__ void series2(cx<R>* z, int s, int g, int Ls, R x, R m
   while (rest > 1) {
     int p = 2;
     while (rest % p != 0) ++p;
-    cx<R> add[2] = {{R(0), R(0)}, {R(0), R(0)}};
+    cx<R> sum[2] = {z[0], z[1]};
     R rj = R(1);
     for (int k = 1; k < p; ++k) {
       const int j = k * n;
@@ -70,10 +71,10 @@ __device__ __forceinline__ void series2(cx<R>* z, int s, int g, int Ls, R x, R m
       const int src = g * Ls + (wrap ? (dn ? t + Ls : t - Ls) : t);
       const R f = wrap ? -m * rj : rj;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) add[c] = cfma_r(f, shfl2(z[c], src), add[c]);
+      for (int c = 0; c < 2; ++c) sum[c] = cfma_r(f, shfl2(z[c], src), sum[c]);
     }
 #pragma unroll
-    for (int c = 0; c < 2; ++c) z[c] = z[c] + add[c];
+    for (int c = 0; c < 2; ++c) z[c] = sum[c];
     rn *= rj;
     n *= p;
     rest /= p;
