@@ -130,7 +130,9 @@ typedef struct {
                           per work-group serve all of them); 0 = autotune                     */
   int32_t waves;       /* waves per work-group in the hop kernels (1, 2, 4); 0 = autotune
                           (rhs_block and waves both 0: the pair is timed on the first solve of
-                          a shape and kept for the process, per device and lattice)          */
+                          a shape and kept for the process, per device and lattice; on
+                          lattices of few tiles another form of the kernels runs then, eight
+                          waves to a tile and one right-hand side per work-group)            */
   int32_t precond;     /* 0: CGNR as above; 1: flexible CG on the normal equations in FP64 with
                           the learned preconditioner `net` (NULL = identity), one right-hand
                           side at a time, falling back to CGNR on breakdown or stagnation     */

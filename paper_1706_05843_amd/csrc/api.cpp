@@ -606,7 +606,7 @@ int inner_iteration(eofa_ctx* C, const Form& F, int S, const HopArgs& k1, const 
   // CG state rides in the next iteration's K1 (8^4 x 8 FP32: 32.4 us an iteration
   // with a finalize launch of its own, 29.6 without; 4^4 x 8 FP64 34.5 and 31.6);
   // the last iteration before the host looks at the state takes a launch for it
-  const bool lean = hop_is_small(S, g.Vh, g.Ls, nrhs);
+  const bool lean = hop_is_small(S, k1);
   if (lean && !first) {
     a1.fin_partial = partial;
     a1.fin_nblk = nbh;
@@ -742,13 +742,14 @@ int autotune(eofa_ctx* C, const Form& F, int S, int nrhs, HopArgs k1, HopArgs k2
 // itself unpacked). Overwrites te, tmp, ro; synchronises.
 int reconstruct(eofa_ctx* C, const Form& F, int nrhs, void* x, void* be, void* bo, void* te, void* tmp, void* ro,
                 double* partial, CgState Sst, void* psi, std::vector<double>& re, std::vector<double>& rodd,
-                hipStream_t st) {
+                hipStream_t st, int shaped = 0) {
   const Geometry& g = C->g;
   re.assign(nrhs, 0.0);
   rodd.assign(nrhs, 0.0);
   // reconstruct psi'_e = M_ee^-1 (b_e - Dhop D~ x_o)
   {
     HopArgs a = base_args(C, P64, 0, nrhs);
+    a.shaped = shaped;
     a.in = x;
     a.z = be;
     a.out = tmp;
@@ -758,6 +759,7 @@ int reconstruct(eofa_ctx* C, const Form& F, int nrhs, void* x, void* be, void* b
   // FP64 true residual of the system on both parities
   {
     HopArgs a = base_args(C, P64, 0, nrhs);
+    a.shaped = shaped;
     a.in = x;
     a.y = te;
     a.z = be;
@@ -769,6 +771,7 @@ int reconstruct(eofa_ctx* C, const Form& F, int nrhs, void* x, void* be, void* b
     launch_finalize(FIN_NORM, partial, nb, nrhs, Sst, Sst.norm, st);
     CHK(fetch(C, Sst.norm, nrhs * sizeof(double), re.data(), st));
     HopArgs b = base_args(C, P64, 1, nrhs);
+    b.shaped = shaped;
     b.in = te;
     b.y = x;
     b.z = bo;
@@ -819,6 +822,18 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
   const bool keep = prm->keep_direction && S != P64 && !fixed;
   if (keep) inner_floor = std::max(inner_floor, S == P16 ? 0.1 : 0.01);
 
+  // a given launch shape (that fits the 160 KB of LDS) asks for the general form of
+  // the hop kernels throughout the solve
+  const int given_W = prm->waves > 0 ? prm->waves : default_waves(g.Ls);
+  int shaped = prm->rhs_block > 0 || prm->waves > 0 ? 1 : 0;
+  for (int role : {F.k1, F.k2, F.k3, F.k4})
+    if (hop_lds_bytes(S, role, g.Ls, given_W) + 256 > 163840) shaped = 0;
+  auto args = [&](int prec, int out_parity) {
+    HopArgs a = base_args(C, prec, out_parity, nrhs);
+    a.shaped = shaped;
+    return a;
+  };
+
   CHK(upload_systems(C, sys, nrhs, st));
   CHK(stage(C, 64 * (size_t)std::max(nrhs, 16)));
   const size_t b64 = packed_bytes(P64, g, nrhs), bS = packed_bytes(S, g, nrhs), bX = packed_bytes(PX, g, nrhs);
@@ -836,7 +851,7 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
   CHK(ws(C, "wS", bS, &wS));
   CHK(ws(C, "rin", bS, &rin));
   CHK(ws(C, "xin", bX, &xin));
-  const int maxblk = std::max(hop_blocks(P64, g.Vh, g.Ls, 1, 1), (g.Ls * g.Vh + 255) / 256);  // W = 1 has the most blocks
+  const int maxblk = std::max(hop_blocks(g.Vh, g.Ls, 1), (g.Ls * g.Vh + 255) / 256);  // W = 1 has the most blocks
   CHK(ws(C, "partial", sizeof(double) * (size_t)maxblk * nrhs, &partial_v));
   double* partial = (double*)partial_v;
   CgState Sst;
@@ -893,7 +908,7 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
   // Schur source b~_o = b_o - Dhop D~ M_ee^-1 b_e (dense: b_o - Dhop D_ee^-1 b_e)
   launch_smat(P64, g, be, te, mats_of(C), F.inv, nrhs, st);
   {
-    HopArgs a = base_args(C, P64, 1, nrhs);
+    HopArgs a = args(P64, 1);
     a.in = te;
     a.z = bo;
     a.out = bt;
@@ -921,24 +936,24 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
     for (auto& ev : C->events) HIPCHK(hipEventCreate(&ev));
   }
 
-  HopArgs k1 = base_args(C, S, 0, nrhs);
+  HopArgs k1 = args(S, 0);
   k1.in = pS;
   k1.out = tS;
   k1.matA = F.m1;
   k1.halt = Sst.halt;
-  HopArgs k2 = base_args(C, S, 1, nrhs);
+  HopArgs k2 = args(S, 1);
   k2.in = tS;
   k2.y = pS;
   k2.out = wS;
   k2.matB = F.m2;
   k2.partial = partial;
   k2.halt = Sst.halt;
-  HopArgs k3 = base_args(C, S, 0, nrhs);
+  HopArgs k3 = args(S, 0);
   k3.in = wS;
   k3.out = tS;
   k3.matA = F.m3;
   k3.halt = Sst.halt;
-  HopArgs k4 = base_args(C, S, 1, nrhs);
+  HopArgs k4 = args(S, 1);
   k4.in = tS;
   k4.y = wS;
   k4.r = rin;
@@ -962,12 +977,12 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
       launch_convert(P64, P64, g, bt, ro, nrhs, st);
       CHK(norms(C, P64, ro, nrhs, partial, Sst, rro, st));
     } else {
-      HopArgs a1 = base_args(C, P64, 0, nrhs);
+      HopArgs a1 = args(P64, 0);
       a1.in = x;
       a1.out = te;
       a1.matA = F.m1;
       CHK(hop(C, P64, F.k1x, a1, st));
-      HopArgs a2 = base_args(C, P64, 1, nrhs);
+      HopArgs a2 = args(P64, 1);
       a2.in = te;
       a2.y = x;
       a2.z = bt;
@@ -1025,12 +1040,12 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
     CHK(put(C, Sst.guard, gd.data(), nrhs * sizeof(double), st));
     launch_convert(P64, S, g, ro, rS, nrhs, st);
     {
-      HopArgs a3 = base_args(C, S, 0, nrhs);
+      HopArgs a3 = args(S, 0);
       a3.in = rS;
       a3.out = tS;
       a3.matA = F.m3;
       CHK(hop(C, S, F.k3, a3, st));
-      HopArgs a4 = base_args(C, S, 1, nrhs);
+      HopArgs a4 = args(S, 1);
       a4.in = tS;
       a4.y = rS;
       a4.r = rin;
@@ -1055,14 +1070,13 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
     launch_zero(PX, g, xin, nrhs, st);
 
     if (prm->rhs_block > 0 || prm->waves > 0) {
-      const int w = prm->waves > 0 ? prm->waves : default_waves(g.Ls);
       const int rb = prm->rhs_block > 0 ? std::min(prm->rhs_block, nrhs) : nrhs;
       for (HopArgs* x : {&k1, &k2, &k3, &k4}) {
-        x->W = w;
+        x->W = given_W;
         x->rhs_block = rb;
       }
     }
-    const int nbh = hop_blocks(S, g.Vh, g.Ls, k1.W, nrhs);
+    const int nbh = hop_blocks(g.Vh, g.Ls, hop_is_small(S, k1) ? 1 : k1.W);
 
     int it = 0;
     const int cap = fixed ? prm->fixed_iters : prm->max_iter + 1;
@@ -1158,7 +1172,7 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
   }
 
   std::vector<double> re, rodd;
-  CHK(reconstruct(C, F, nrhs, x, be, bo, te, tmp, ro, partial, Sst, psi, re, rodd, st));
+  CHK(reconstruct(C, F, nrhs, x, be, bo, te, tmp, ro, partial, Sst, psi, re, rodd, st, shaped));
   const double t1 = now_s();
   for (int j = 0; j < timed; ++j) {  // events are read only after the solve: no mid-solve host stalls
     float ms;
@@ -1227,7 +1241,7 @@ int eofa::normal_op_fp32(eofa_ctx* C, const eofa_system* sys, const void* in, vo
   void *te, *w, *pv;
   CHK(ws(C, "na_te", b32, &te));
   CHK(ws(C, "na_w", b32, &w));
-  const int maxblk = std::max(hop_blocks(P32, g.Vh, g.Ls, 1, 1), (g.Ls * g.Vh + 255) / 256);
+  const int maxblk = std::max(hop_blocks(g.Vh, g.Ls, 1), (g.Ls * g.Vh + 255) / 256);
   CHK(ws(C, "na_partial", sizeof(double) * (size_t)maxblk, &pv));
   HopArgs k1 = base_args(C, P32, 0, 1);
   k1.in = in;
@@ -1314,7 +1328,7 @@ struct Fgcg {
     for (int k = 0; k < 12; ++k) CHK(ws(C, names[k], b64, bufs[k]));
     CHK(ws(C, "fg_r32", b32, &r32));
     CHK(ws(C, "fg_z32", b32, &z32));
-    const int maxblk = std::max({hop_blocks(P64, g.Vh, g.Ls, 1, 1), (g.Ls * g.Vh + 255) / 256, 512 * FG_CHUNK});
+    const int maxblk = std::max({hop_blocks(g.Vh, g.Ls, 1), (g.Ls * g.Vh + 255) / 256, 512 * FG_CHUNK});
     void* pv;
     CHK(ws(C, "fg_partial", sizeof(double) * 2 * (size_t)maxblk, &pv));
     partial = (double*)pv;
@@ -1677,7 +1691,7 @@ extern "C" int eofa_cg_solve_noalloc(eofa_ctx* C, const eofa_system* sys, const 
   const Geometry& g = C->g;
   const int S = prm->inner_prec, PX = S == P64 ? P64 : P32;
   const size_t b64 = packed_bytes(P64, g, nrhs), bS = packed_bytes(S, g, nrhs), bX = packed_bytes(PX, g, nrhs);
-  const size_t maxblk = std::max(hop_blocks(P64, g.Vh, g.Ls, 1, 1), (g.Ls * g.Vh + 255) / 256);
+  const size_t maxblk = std::max(hop_blocks(g.Vh, g.Ls, 1), (g.Ls * g.Vh + 255) / 256);
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   const size_t need = 7 * al(b64) + 5 * al(bS) + al(bX) + al(sizeof(double) * maxblk * nrhs) +
                       al((8 * sizeof(double) + 5 * sizeof(int)) * nrhs + 64) +
@@ -1772,7 +1786,7 @@ int forecast(eofa_ctx* C, const eofa_system* sys, const void* rhs, const std::ve
   CHK(ws(C, "fc_mo", b64, &mo));
   CHK(ws(C, "fc_zero", b64, &zero));
   CHK(ws(C, "fc_g5", 2 * b64 * (size_t)N, &g5));
-  const int maxblk = std::max({hop_blocks(P64, g.Vh, g.Ls, 1, 1), (g.Ls * g.Vh + 255) / 256, 2048});
+  const int maxblk = std::max({hop_blocks(g.Vh, g.Ls, 1), (g.Ls * g.Vh + 255) / 256, 2048});
   CHK(ws(C, "fc_partial", sizeof(double) * 2 * (size_t)maxblk, &pv));
   CHK(ws(C, "fc_dot", sizeof(double) * (4 * (size_t)N * N + 2 * (size_t)N), &dv));
   CHK(stage(C, sizeof(double) * (4 * (size_t)N * N + 2 * (size_t)N)));

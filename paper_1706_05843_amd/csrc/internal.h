@@ -122,6 +122,7 @@ struct HopArgs {
   double* partial;    // [nrhs][gridDim.x]
   int Vh, Ls, nrhs, rhs_block;
   int W;              // waves per work-group (1, 2 or 4)
+  int shaped;         // 1: W and rhs_block were asked for: the general form at any size
   int nt_out;         // 1: non-temporal output stores (set by the launcher)
   // optional CG step fused into a K3 (or D3) launch: work-group 0 of each RHS block
   // reduces fin_partial [nrhs][fin_nblk] (the previous launch's partial
@@ -134,11 +135,13 @@ struct HopArgs {
 
 // kernel launchers (kernels.hip)
 int launch_hop(int prec, int role, const HopArgs& a, hipStream_t st, int* nblk_out);
-// the same for launches that hop_is_small takes (hop_small.hip)
+// the same for launches that hop_is_small takes (hop_small.hip): those of few tiles
+// for which no shape was asked
 int launch_hop_small(int prec, int role, const HopArgs& a, hipStream_t st);
-bool hop_is_small(int prec, int Vh, int Ls, int nrhs);
-// work-groups of a launch per right-hand side (one partial sum each)
-int hop_blocks(int prec, int Vh, int Ls, int W, int nrhs);
+bool hop_is_small(int prec, const HopArgs& a);
+// work-groups per right-hand side (one partial sum each) for W waves per
+// work-group; the small form has those of W = 1
+int hop_blocks(int Vh, int Ls, int W);
 // default waves per work-group for Ls (at most 20 4D sites per work-group)
 int default_waves(int Ls);
 // LDS bytes the hop kernel of this role needs, for the precision and shape

@@ -1267,13 +1267,13 @@ constexpr int acc_prec() {
 // Ls = 16, whose row form here is faster, FP16S 29 and 35 at 32 tiles, 38 and 40 at 512,
 // and at 2048 180 and 129 / 93 and 71 / 79 and 55. The single hop in FP64 is level
 // at 820.
-bool hop_is_small(int prec, int Vh, int Ls, int nrhs) {
-  const size_t G = sites_per_wave(Ls), tiles = ((size_t)Vh + G - 1) / G;
-  return tiles * nrhs <= (prec == P64 ? 640u : 1024u) / (Ls == 16 ? 2 : 1);
+bool hop_is_small(int prec, const HopArgs& a) {
+  if (a.shaped) return false;
+  const size_t G = sites_per_wave(a.Ls), tiles = ((size_t)a.Vh + G - 1) / G;
+  return tiles * a.nrhs <= (prec == P64 ? 640u : 1024u) / (a.Ls == 16 ? 2 : 1);
 }
 
-int hop_blocks(int prec, int Vh, int Ls, int W, int nrhs) {
-  if (hop_is_small(prec, Vh, Ls, nrhs)) W = 1;
+int hop_blocks(int Vh, int Ls, int W) {
   const int SBk = W * sites_per_wave(Ls);
   return (Vh + SBk - 1) / SBk;
 }
@@ -1349,7 +1349,7 @@ int launch_hop_t(const HopArgs& a, hipStream_t st, int* nblk_out) {
   const int Ls = a.Ls;
   const int W = a.W >= 1 && a.W <= MAXW ? a.W : default_waves(Ls);
   const size_t lds = hop_lds_t<P, ROLE>(Ls, W);
-  const int nblk = hop_blocks(P, a.Vh, Ls, W, a.nrhs);
+  const int nblk = hop_blocks(a.Vh, Ls, W);
   const int rb = a.rhs_block > 0 ? a.rhs_block : 1;
   dim3 grid(nblk, (a.nrhs + rb - 1) / rb);
   HopArgs b = a;
@@ -1398,8 +1398,8 @@ int launch_hop_p(int role, const HopArgs& a, hipStream_t st, int* nb) {
 }
 
 int launch_hop(int prec, int role, const HopArgs& a, hipStream_t st, int* nblk_out) {
-  if (hop_is_small(prec, a.Vh, a.Ls, a.nrhs)) {
-    if (nblk_out) *nblk_out = hop_blocks(prec, a.Vh, a.Ls, 1, a.nrhs);
+  if (hop_is_small(prec, a)) {
+    if (nblk_out) *nblk_out = hop_blocks(a.Vh, a.Ls, 1);
     return launch_hop_small(prec, role, a, st);
   }
   switch (prec) {
