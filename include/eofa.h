@@ -176,7 +176,8 @@ typedef struct {
                            [2] M_ee^-T D~^T Dhop^dag, [3] residual update       */
   int32_t hop_timed;    /* profile=1: inner iterations whose kernels were timed */
   int32_t waves;        /* launch shape the inner hop kernels used: waves and   */
-  int32_t rhs_block;    /* right-hand sides per work-group (autotuned or given) */
+  int32_t rhs_block;    /* right-hand sides per work-group (autotuned or given;
+                           8 and 1 in the form for few tiles)                  */
   int32_t fell_back;    /* precond = 1: 1 if the solve fell back to CGNR        */
 } eofa_solver_stats;
 

@@ -962,7 +962,8 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
   k4.alpha = Sst.alpha;
   k4.partial = partial;
   k4.halt = Sst.halt;
-  if (prm->rhs_block <= 0 && prm->waves <= 0 && !C->arena) {
+  const bool small = hop_is_small(S, k1);  // one shape: nothing to tune
+  if (prm->rhs_block <= 0 && prm->waves <= 0 && !C->arena && !small) {
     CHK(autotune(C, F, S, nrhs, k1, k2, k3, k4, st));
     const auto pick = C->tuned[tune_key(F, S, nrhs)];
     for (HopArgs* x : {&k1, &k2, &k3, &k4}) {
@@ -1076,7 +1077,7 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
         x->rhs_block = rb;
       }
     }
-    const int nbh = hop_blocks(g.Vh, g.Ls, hop_is_small(S, k1) ? 1 : k1.W);
+    const int nbh = hop_blocks(g.Vh, g.Ls, small ? 1 : k1.W);
 
     int it = 0;
     const int cap = fixed ? prm->fixed_iters : prm->max_iter + 1;
@@ -1198,8 +1199,8 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
       o.seconds = t1 - t0;
       for (int k = 0; k < 4; ++k) o.hop_ms[k] = hop_ms[k];
       o.hop_timed = timed;
-      o.waves = k1.W;
-      o.rhs_block = k1.rhs_block;
+      o.waves = small ? 8 : k1.W;
+      o.rhs_block = small ? 1 : k1.rhs_block;
     }
     if (status[r] != EOFA_OK && (worst == EOFA_OK || status[r] == EOFA_ERR_BREAKDOWN)) worst = status[r];
   }

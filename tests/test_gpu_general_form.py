@@ -105,3 +105,15 @@ def test_one_halted_in_a_shared_work_group(Ls, prec):
     assert st[0]["waves"] == 2 and st[0]["rhs_block"] == 3
     assert np.all(got[1] == 0.0)
     assert rel2(got[0], ref[0]) < 1e-13 and rel2(got[2], ref[1]) < 1e-13
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_shape_reported_for_few_tiles(noalloc):
+    """Without a given shape few tiles take the eight-wave form, nothing to tune."""
+    act, U, phi, ctx = setup(8)
+    ph = torch.from_numpy(phi).cuda()
+    psi = torch.zeros_like(ph)
+    call = ctx.eofa_cg_solve_noalloc if noalloc else ctx.eofa_cg_solve
+    rc, st = call(SYSTEMS, ph, psi, eofa.make_params(tol=1e-10))
+    assert rc == eofa.EOFA_OK
+    assert all((s["waves"], s["rhs_block"]) == (8, 1) for s in st)
