@@ -231,7 +231,7 @@ HopArgs base_args(eofa_ctx* C, int prec, int out_parity, int nrhs) {
   std::memset(&a, 0, sizeof(a));
   a.links = C->links[prec][out_parity];
   a.nbr = C->nbr[out_parity];
-  a.order = C->order;
+  a.order = C->order[prec == P16];
   a.mats = mats_of(C);
   a.matA = 0;
   a.matB = 0;
@@ -355,15 +355,19 @@ int eofa_create(const eofa_action* act, const void* gauge, void* stream, eofa_ct
       eofa_destroy(C);
       return fail(EOFA_ERR_OOM, "hipMalloc failed for neighbour table");
     }
-  if (hipMalloc((void**)&C->order, (size_t)C->g.Vh * sizeof(int)) != hipSuccess) {
-    (void)hipGetLastError();
-    eofa_destroy(C);
-    return fail(EOFA_ERR_OOM, "hipMalloc failed for the traversal order");
-  }
-  {
+  for (int k = 0; k < 2; ++k) {
+    if (k == 1 && order_dealt(C->g, P16) == order_dealt(C->g, P64)) {
+      C->order[1] = C->order[0];
+      break;
+    }
+    if (hipMalloc((void**)&C->order[k], (size_t)C->g.Vh * sizeof(int)) != hipSuccess) {
+      (void)hipGetLastError();
+      eofa_destroy(C);
+      return fail(EOFA_ERR_OOM, "hipMalloc failed for the traversal order");
+    }
     std::vector<int> ord(C->g.Vh);
-    site_order(C->g, ord.data());
-    if (hipMemcpy(C->order, ord.data(), ord.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess) {
+    site_order(C->g, k == 1 ? P16 : P64, ord.data());
+    if (hipMemcpy(C->order[k], ord.data(), ord.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess) {
       eofa_destroy(C);
       return fail(EOFA_ERR_HIP, "traversal order upload failed");
     }
@@ -400,7 +404,8 @@ int eofa_destroy(eofa_ctx* C) {
       if (C->links[p][par]) (void)hipFree(C->links[p][par]);
   for (int par = 0; par < 2; ++par)
     if (C->nbr[par]) (void)hipFree(C->nbr[par]);
-  if (C->order) (void)hipFree(C->order);
+  if (C->order[1] && C->order[1] != C->order[0]) (void)hipFree(C->order[1]);
+  if (C->order[0]) (void)hipFree(C->order[0]);
   for (auto& kv : C->pool)
     if (kv.second.p) (void)hipFree(kv.second.p);
   if (C->mats) (void)hipFree(C->mats);

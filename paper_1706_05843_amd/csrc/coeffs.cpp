@@ -247,19 +247,29 @@ int build_fifth(const Geometry& g, double M5, double b5, double c5, const eofa_s
 // likewise; each row contributes its Lx/2 sites of one parity in x order.
 //
 // The hop kernels give each of the 8 XCDs a contiguous eighth of the positions.
-// With the blocks in plain lexicographic order the XCDs sweep eight far-apart
-// t ranges, whose windows of three t slabs together overflow the 256 MB MALL on
-// large lattices, so the t neighbours come from HBM again. There (kSweep 5D
-// sites of a parity and more) the blocks are dealt out slab by slab: every XCD
-// takes an eighth of each bt-thick t slab and all sweep t together, sharing one
-// window. Measured, one card, 24^3 x 64, Ls = 12, plain order against this one:
-// FP64 958 -> 907 us, FP32 436 -> 416, FP16S 273 -> 260; at 16^3 x 32, Ls = 16
-// (1.05 M sites, fields within the MALL) it is level, and at 8 x 12 x 6 x 16,
-// Ls = 8 it costs 7 %: each XCD's eighth of a slab is then a few rows, most of
-// whose neighbours belong to other XCDs.
-constexpr size_t kSweep = 1500000;
+// With the blocks in plain lexicographic order the XCDs sweep eight far-apart t
+// ranges, each with a window of three bt-thick t slabs it still reads. Where these
+// 24 slabs (or the field, if it is smaller) overflow the 256 MB MALL, the t
+// neighbours come from HBM again, and the blocks are dealt out slab by slab
+// instead: every XCD takes an eighth of each slab and all sweep t together, sharing
+// one window. Where they fit, dealing only cuts each XCD's part of a slab down
+// until most of its neighbours belong to other XCDs. The line lies at 1.5 M 5D
+// sites of a parity (FP64 fields of 288 MB); for FP16S, whose fields are a quarter
+// of that, at 2 M. Dslash, one card, us, plain order / dealt out, FP64, FP32, FP16S:
+//   24^3 x 64, Ls = 12 (slab 0.33 M, 5.3 M in all) 949 / 898, 438 / 422, 264 / 255
+//   16^3 x 64, Ls = 16 (0.13 M, 2.1 M)             354 / 331, 142 / 142, 75 / 68
+//   16 x 16 x 8 x 192, Ls = 16 (0.066 M, 3.1 M)    490 / 465, 227 / 221, 140 / 137
+//   18 x 14 x 22 x 26, Ls = 24 (0.13 M, 1.7 M)     331 / 317, 124 / 126, 72 / 74
+//   16^3 x 48, Ls = 16 (0.13 M, 1.6 M)             251 / 250, 87 / 93, 53 / 55
+//   12^3 x 128, Ls = 16 (0.055 M, 1.8 M)           283 / 284, 91 / 103, 57 / 60
+//   8^3 x 256, Ls = 32 (0.033 M, 2.1 M)            323 / 331, 112 / 140, 66 / 75
+//   4^3 x 2048, Ls = 32 (0.004 M, 2.1 M)           308 / 369, 109 / 164, 68 / 84
+bool order_dealt(const Geometry& g, int prec) {
+  const size_t sites = (size_t)g.Vh * g.Ls, slab = sites / g.L[3] * (g.L[3] % 4 == 0 ? 4 : 2);
+  return std::min(sites, 24 * slab) >= (prec == P16 ? 2000000u : 1500000u);
+}
 
-void site_order(const Geometry& g, int* out) {
+void site_order(const Geometry& g, int prec, int* out) {
   auto blk = [](int L) { return L % 4 == 0 ? 4 : (L % 2 == 0 ? 2 : 1); };
   const int Lxh = g.L[0] / 2, Ly = g.L[1], Lz = g.L[2], Lt = g.L[3];
   const int by = blk(Ly), bz = blk(Lz), bt = blk(Lt);
@@ -275,7 +285,7 @@ void site_order(const Geometry& g, int* out) {
               const int row = (t * Lz + z) * Ly + y;
               for (int xh = 0; xh < Lxh; ++xh) base.push_back(row * Lxh + xh);
             }
-  if ((size_t)g.Vh * g.Ls < kSweep) {
+  if (!order_dealt(g, prec)) {
     std::copy(base.begin(), base.end(), out);
     return;
   }

@@ -196,8 +196,10 @@ void launch_heatbath_combine(const Geometry& g, const void* eta, const void* sol
 
 size_t packed_bytes(int prec, const Geometry& g, int nrhs);
 // traversal order of the hop kernels (host): position k -> checkerboard index
-// i = row * Lx/2 + xh, x-rows visited in (y, z, t) blocks of up to 4^3
-void site_order(const Geometry& g, int* out);
+// i = row * Lx/2 + xh, x-rows visited in (y, z, t) blocks of up to 4^3, dealt out to
+// the XCDs slab by slab where order_dealt
+bool order_dealt(const Geometry& g, int prec);
+void site_order(const Geometry& g, int prec, int* out);
 size_t link_bytes(int prec, const Geometry& g);
 
 }  // namespace eofa
@@ -229,7 +231,9 @@ struct eofa_ctx {
   int device;
   void* links[3][2] = {{nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}};
   int* nbr[2] = {nullptr, nullptr};
-  int* order = nullptr;  // hop-kernel traversal order (site_order), [Vh]
+  // hop-kernel traversal order (site_order), [Vh]: of FP64 and FP32, and of FP16S
+  // (the same array where the two agree)
+  int* order[2] = {nullptr, nullptr};
   // G-parity in x: the lattice is held x-doubled (flavour f at x + f Lx) with
   // links [U, conj(U)] and an antiperiodic x edge; Lx_phys is the physical Lx
   bool gparity = false;

@@ -144,7 +144,7 @@ void run_layer(eofa_ctx* C, eofa_net* N, int l, bool adj, void* const* in, void*
   a.w = N->wb + 2 * N->woff[l];
   a.links = (const float*)C->links[P32][parity];
   a.nbr = C->nbr[parity];
-  a.order = C->order;
+  a.order = C->order[0];
   a.Vh = C->g.Vh;
   a.Ls = C->g.Ls;
   a.Cin = adj ? N->ch[l + 1] : N->ch[l];
@@ -162,7 +162,7 @@ void run_wgrad(eofa_ctx* C, eofa_net* N, int l, void* const* x, void* const* g, 
     ga.links[p] = (const float*)C->links[P32][p];
     ga.nbr[p] = C->nbr[p];
   }
-  ga.order = C->order;
+  ga.order = C->order[0];
   ga.partial = N->partial;
   ga.Vh = C->g.Vh;
   ga.Ls = C->g.Ls;
