@@ -611,7 +611,7 @@ int inner_iteration(eofa_ctx* C, const Form& F, int S, const HopArgs& k1, const 
   // CG state rides in the next iteration's K1 (8^4 x 8 FP32: 32.4 us an iteration
   // with a finalize launch of its own, 29.6 without; 4^4 x 8 FP64 34.5 and 31.6);
   // the last iteration before the host looks at the state takes a launch for it
-  const bool lean = hop_is_small(S, k1);
+  const bool lean = hop_is_small(S, F.k1, k1);
   if (lean && !first) {
     a1.fin_partial = partial;
     a1.fin_nblk = nbh;
@@ -967,7 +967,7 @@ int solve_batch(eofa_ctx* C, const eofa_system* sys, int nrhs, const void* phi, 
   k4.alpha = Sst.alpha;
   k4.partial = partial;
   k4.halt = Sst.halt;
-  const bool small = hop_is_small(S, k1);  // one shape: nothing to tune
+  const bool small = hop_is_small(S, F.k1, k1);  // one shape: nothing to tune
   if (prm->rhs_block <= 0 && prm->waves <= 0 && !C->arena && !small) {
     CHK(autotune(C, F, S, nrhs, k1, k2, k3, k4, st));
     const auto pick = C->tuned[tune_key(F, S, nrhs)];

@@ -138,7 +138,7 @@ int launch_hop(int prec, int role, const HopArgs& a, hipStream_t st, int* nblk_o
 // the same for launches that hop_is_small takes (hop_small.hip): those of few tiles
 // for which no shape was asked
 int launch_hop_small(int prec, int role, const HopArgs& a, hipStream_t st);
-bool hop_is_small(int prec, const HopArgs& a);
+bool hop_is_small(int prec, int role, const HopArgs& a);
 // work-groups per right-hand side (one partial sum each) for W waves per
 // work-group; the small form has those of W = 1
 int hop_blocks(int Vh, int Ls, int W);

@@ -1267,10 +1267,22 @@ constexpr int acc_prec() {
 // Ls = 16, whose row form here is faster, FP16S 29 and 35 at 32 tiles, 38 and 40 at 512,
 // and at 2048 180 and 129 / 93 and 71 / 79 and 55. The single hop in FP64 is level
 // at 820.
-bool hop_is_small(int prec, const HopArgs& a) {
+// The dense roles multiply by an Ls x Ls matrix read row by row from the caches
+// there, from LDS here, so below FP64 their line falls with Ls (DENSE_LS tiles times
+// Ls), and at Ls = 32, whose rows lie 256 bytes apart, to DENSE_32 tiles. FP32 / FP16S
+// iterations of the dense form there and here: Ls = 32, 256 tiles 45 and 61 / 44 and
+// 58, 384 tiles 68 and 64 / 66 and 60, 1024 131 and 73 / 115 and 66; Ls = 24, 576
+// tiles 55 and 59 / 51 and 54, 1024 73 and 63 / 64 and 56; Ls = 20, 683 tiles 52 and
+// 60 / 48 and 53.
+constexpr size_t DENSE_LS = 16384, DENSE_32 = 256;
+
+bool hop_is_small(int prec, int role, const HopArgs& a) {
   if (a.shaped) return false;
-  const size_t G = sites_per_wave(a.Ls), tiles = ((size_t)a.Vh + G - 1) / G;
-  return tiles * a.nrhs <= (prec == P64 ? 640u : 1024u) / (a.Ls == 16 ? 2 : 1);
+  const size_t G = sites_per_wave(a.Ls), tiles = ((size_t)a.Vh + G - 1) / G * a.nrhs;
+  const bool dense = role == ROLE_D1 || role == ROLE_D2 || role == ROLE_D3 || role == ROLE_D4 || role == ROLE_D4S ||
+                     role == ROLE_DRES || role == ROLE_DFULLRES;
+  if (dense && prec != P64 && (a.Ls == 32 ? tiles > DENSE_32 : tiles * a.Ls > DENSE_LS)) return false;
+  return tiles <= (prec == P64 ? 640u : 1024u) / (a.Ls == 16 ? 2 : 1);
 }
 
 int hop_blocks(int Vh, int Ls, int W) {
@@ -1398,7 +1410,7 @@ int launch_hop_p(int role, const HopArgs& a, hipStream_t st, int* nb) {
 }
 
 int launch_hop(int prec, int role, const HopArgs& a, hipStream_t st, int* nblk_out) {
-  if (hop_is_small(prec, a)) {
+  if (hop_is_small(prec, role, a)) {
     if (nblk_out) *nblk_out = hop_blocks(a.Vh, a.Ls, 1);
     return launch_hop_small(prec, role, a, st);
   }

@@ -117,3 +117,21 @@ def test_shape_reported_for_few_tiles(noalloc):
     rc, st = call(SYSTEMS, ph, psi, eofa.make_params(tol=1e-10))
     assert rc == eofa.EOFA_OK
     assert all((s["waves"], s["rhs_block"]) == (8, 1) for s in st)
+
+
+@pytest.mark.parametrize("Ls,dims,n,few", [(32, (4, 2, 2, 2), 32, True), (32, (4, 2, 2, 2), 33, False),
+                                           (24, (4, 2, 2, 2), 85, True), (24, (4, 2, 2, 2), 86, False),
+                                           (8, (4, 2, 2, 2), 512, True), (8, (4, 2, 2, 2), 513, False)])
+def test_dense_roles_line(Ls, dims, n, few):
+    """The dense form leaves the eight-wave kernels at fewer tiles the larger Ls is (256
+    tiles at 32, 16384 / Ls below); the Cayley form of the same batch stays."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    ctx = eofa.Context(eofa.make_action(dims, Ls, M5, B5, C5), torch.from_numpy(synth.unit_gauge(dims)).cuda())
+    phi = synth.fermion_torch(dims, Ls, 5, nrhs=n)
+    psi = torch.empty_like(phi)
+    for form in (0, 1):
+        _, st = ctx.eofa_cg_solve([SYSTEMS[2]] * n, phi, psi,
+                                  eofa.make_params(fixed_iters=1, inner_prec=eofa.FP32, form=form))
+        assert (st[0]["waves"] == 8) == (few or (form == 0 and Ls != 8)), form
+    ctx.close()
