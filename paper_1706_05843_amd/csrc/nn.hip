@@ -232,7 +232,9 @@ __global__ void __launch_bounds__(256) pt_layer_kernel(NetLayerArgs a) {
 // error of a whole network against 64 bits, FP32 multiply-adds / MFMA into the
 // accumulator / as here: 1,8,8,8,1 at 16^3 x 32 x 16 3.7e-7 / 5.9e-7 / 2.5e-7,
 // 1,4,1 2.1e-7 / 2.8e-7 / 1.7e-7, 1,3,2,1 at 8^4 x 8 3.6e-7 / 2.8e-7 / 2.1e-7.
-// An infinite activation becomes NaN in the split.
+// An infinite activation becomes NaN in the split (of every row of its products): a
+// lane whose sums hold one does its outputs over as plain FP32 products, which keep
+// the infinity (mf_plain).
 // What bounds it: vector instructions (5600 per wave and tile of 16 5D sites:
 // transports 288 and splits 264 of each pass), busy about two thirds of the
 // time, then the matrix cores (15 %). Taking two channels of all directions per
@@ -395,11 +397,51 @@ __device__ __forceinline__ void mf_pass(const MfIn& x, const float2* L, const w4
   }
 }
 
+// Output channels c0 .. c0 + nc - 1 of one 5D site as plain FP32 products, for the
+// few sites whose operands the split does not carry. Rolled up: its speed does not
+// matter, its registers must not weigh on the kernel around it.
+template <bool ADJ>
+__device__ __forceinline__ void mf_plain(const NetLayerArgs& a, int k5, int s, int c0, int nc) {
+  const int i = a.order[k5], Ls = a.Ls, p = a.parity;
+  const FD fin = {Ls, a.Vh, a.Cin}, fo = {Ls, a.Vh, a.Cout};
+  const int sm = s == 0 ? Ls - 1 : s - 1, sp = s == Ls - 1 ? 0 : s + 1;
+#pragma unroll 1
+  for (int co = c0; co < min(c0 + nc, a.Cout); ++co) {
+    cx<float> y[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) y[k] = {0.f, 0.f};
+#pragma unroll 1
+    for (int ci = 0; ci < a.Cin; ++ci) {
+      cx<float> v[12], w[12];
+      ld_spinor<P32>(a.xin[p], fin, ci, s, i, v);
+      ld_half32(a.xin[p], fin, ci, ADJ ? sp : sm, i, 0, w);
+      ld_half32(a.xin[p], fin, ci, ADJ ? sm : sp, i, 1, w);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const cx<float> wv = wload<ADJ>(a, h, co, ci), ww = wload<ADJ>(a, 18 + h, co, ci);
+#pragma unroll
+        for (int k = 6 * h; k < 6 * h + 6; ++k) y[k] = cfma(ww, w[k], cfma(wv, v[k], y[k]));
+      }
+#pragma unroll 1
+      for (int e = 0; e < 8; ++e) {
+        ld_spinor<P32>(a.xin[1 - p], fin, ci, s, a.nbr[(size_t)i * 8 + e], v);
+        link_mul((const float2*)a.links + ((size_t)i * 8 + e) * 9, v);
+        gamma_mul(e & 3, v, w);
+        const int te = ADJ ? (e ^ 4) : e;  // T_e^dag = T_{e^4}
+        const cx<float> wv = wload<ADJ>(a, 2 + te, co, ci), ww = wload<ADJ>(a, 10 + te, co, ci);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) y[k] = cfma(ww, w[k], cfma(wv, v[k], y[k]));
+      }
+    }
+    st_spinor<P32>(a.yout, fo, co, s, i, y);
+  }
+}
+
 template <bool ADJ, int NCO>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) pt_mfma_kernel(NetLayerArgs a, bool nt) {
   extern __shared__ w4_t s_frag[];  // [npair * 8 + 2][64]
   __shared__ float2 s_link[4 * MF_SITES * MF_LSTR];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 15, g = lane >> 4;
   const int npair = (a.Cin + 1) / 2;
   for (int j = tid; j < (npair * 8 + 2) * 64; j += 256) {
     const int f = j >> 6;
@@ -479,6 +521,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))
           st_spinor_nt<P32>(a.yout, fo, NCO * g + ch, s, i, y);
         else
           st_spinor<P32>(a.yout, fo, NCO * g + ch, s, i, y);
+      }
+      float sum = 0.f;
+#pragma unroll
+      for (int k = 0; k < 12; ++k) sum += acc[k][0];
+      if (!isfinite(sum)) {
+        int id = tid;
+        asm volatile("" : "+v"(id));  // nothing is kept in registers for this
+        const int at = tile * 64 + (id >> 6) * 16 + (id & 15);
+        mf_plain<ADJ>(a, at / Ls, at % Ls, NCO * ((id >> 4) & 3), NCO);
       }
     }
   }
