@@ -232,9 +232,10 @@ __global__ void __launch_bounds__(256) pt_layer_kernel(NetLayerArgs a) {
 // error of a whole network against 64 bits, FP32 multiply-adds / MFMA into the
 // accumulator / as here: 1,8,8,8,1 at 16^3 x 32 x 16 3.7e-7 / 5.9e-7 / 2.5e-7,
 // 1,4,1 2.1e-7 / 2.8e-7 / 1.7e-7, 1,3,2,1 at 8^4 x 8 3.6e-7 / 2.8e-7 / 2.1e-7.
-// An infinite activation becomes NaN in the split (of every row of its products): a
-// lane whose sums hold one does its outputs over as plain FP32 products, which keep
-// the infinity (mf_plain).
+// Two things the split does not carry: an infinite activation becomes NaN (in every
+// row of its products), and the matrix cores take a part below 2^-126 as zero, so that
+// activations below 2^-102 lose digits. A lane whose sums hold a NaN or lie below
+// MF_TINY (2^12 above that line) does its outputs over as plain FP32 products (mf_plain).
 // What bounds it: vector instructions (5600 per wave and tile of 16 5D sites:
 // transports 288 and splits 264 of each pass), busy about two thirds of the
 // time, then the matrix cores (15 %). Taking two channels of all directions per
@@ -252,6 +253,7 @@ constexpr int MF_MAXP = (NET_MAXC + 1) / 2;      // channel pairs
 constexpr int MF_FRAGS = MF_MAXP * 8 + 2;        // [pair of channels][mu class][spin pair][output], same-site upper, lower
 constexpr int MF_SITES = 9;                      // most 4D sites 16 consecutive 5D sites touch (Ls >= 2)
 constexpr int MF_LSTR = 73;                      // link stride in LDS
+constexpr float MF_TINY = 0x1p-90f;              // largest sum that is looked at again
 
 __device__ __forceinline__ f32x4_t mf_mul(w4_t A, w4_t B, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8_t, A), __builtin_bit_cast(b8_t, B), c, 0, 0, 0);
@@ -522,10 +524,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))
         else
           st_spinor<P32>(a.yout, fo, NCO * g + ch, s, i, y);
       }
-      float sum = 0.f;
+      float sum = 0.f, top = 0.f;
 #pragma unroll
-      for (int k = 0; k < 12; ++k) sum += acc[k][0];
-      if (!isfinite(sum)) {
+      for (int k = 0; k < 12; ++k) {
+        sum += acc[k][0];
+        top = fmaxf(top, fabsf(acc[k][0]));
+      }
+      if (!isfinite(sum) || (top > 0.f && top < MF_TINY)) {
         int id = tid;
         asm volatile("" : "+v"(id));  // nothing is kept in registers for this
         const int at = tile * 64 + (id >> 6) * 16 + (id & 15);

@@ -68,3 +68,25 @@ def test_overflow_stays_infinite(C, big):
         assert np.isinf(got[k].imag) and np.sign(got[k].imag) == np.sign(w.imag), (s, got[k])
     assert np.isfinite(got[~reached]).all()
     assert np.abs(got - ref)[~reached].max() < 1e-5 * np.abs(ref).max()
+
+
+# Activations near the bottom of the FP32 range (the low parts of whose splits are not
+# normal numbers): N is linear, and a source scaled by a power of two gives the scaled
+# result to the rounding of the layers, 1e-5 of the largest as above, as long as the
+# source itself is represented (its largest entries are normal numbers).
+@pytest.mark.parametrize("k", [100, 112, 120])
+@pytest.mark.parametrize("channels", [[1, 5, 1], [1, 8, 8, 1]])
+def test_tiny_activations(channels, k):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    U = synth.gauge_field(DIMS, 0.5, 18)
+    ctx = eofa.Context(eofa.make_action(DIMS, LS, 1.8, 1.5, 0.5, BC), torch.from_numpy(U).cuda())
+    net = eofa.Net(ctx, channels, seed=2, init_scale=0.25)
+    r = torch.from_numpy(synth.fermion(DIMS, LS, 6)[None]).cuda()
+    out = []
+    for f in (1.0, 2.0 ** -k):
+        pin, pout = ctx.new_packed(eofa.FP32), ctx.new_packed(eofa.FP32)
+        ctx.eofa_pack(r * f, pin, 1, eofa.FP32)
+        net.apply(ctx, pin, pout)
+        out.append(pout.view(torch.float32).double() / f)
+    assert float((out[1] - out[0]).abs().max()) < 1e-5 * float(out[0].abs().max())
