@@ -265,6 +265,7 @@ HopArgs base_args(eofa_ctx* C, int prec, int out_parity, int nrhs) {
     a.rhs_block = std::min(nrhs, 2);
   else
     a.rhs_block = nrhs;
+  a.rhs_block = std::max(a.rhs_block, (nrhs + 65534) / 65535);  // a grid holds 65535 blocks of them
   a.W = default_waves(C->g.Ls);
   auto it = C->tuned.find(prec * 4096 + nrhs);
   if (it != C->tuned.end()) {
