@@ -200,6 +200,7 @@ template <int P, int ROLE>
 __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
   using RT = RoleT<ROLE>;
   using R = typename ST<P>::R;
+  static_assert(P != P16 || RT::OM != O_ADDZ, "sources and true residuals are FP64");
   constexpr bool FIN = ROLE == ROLE_K3 || ROLE == ROLE_D3 || ROLE == ROLE_K1T || ROLE == ROLE_D1;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   cx<R>* s_g = (cx<R>*)smem;  // [direction][component of the half spinor][lane]
@@ -247,8 +248,8 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
       y[0] = t.sc * half_cx(t.w.x);
       y[1] = t.sc * half_cx(t.w.y);
     }
-    if ((RT::OM == O_ADDZ || RT::OM == O_RUPD) && q < 6) {
-      const Pair16 t = ld_pair16(RT::OM == O_ADDZ ? a.z : a.r, fd, r, q, s, site);
+    if (RT::OM == O_RUPD && q < 6) {
+      const Pair16 t = ld_pair16(a.r, fd, r, q, s, site);
       z[0] = half_cx(t.w.x);
       z[1] = half_cx(t.w.y);
       zsc = t.sc;
@@ -446,7 +447,7 @@ __global__ void __launch_bounds__(64 * SMW) hop_small_kernel(HopArgs a) {
     }
     if constexpr (RT::OM == O_ADDZ) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) w[t] = (P == P16 ? (R)zsc * z[t] : z[t]) - w[t];
+      for (int t = 0; t < 2; ++t) w[t] = z[t] - w[t];
     } else if constexpr (RT::OM == O_RUPD) {  // w carries -alpha
 #pragma unroll
       for (int t = 0; t < 2; ++t) w[t] = P == P16 ? cfma_r((R)zsc, z[t], w[t]) : z[t] + w[t];
@@ -504,32 +505,38 @@ int launch_small_t(const HopArgs& a, hipStream_t st) {
   return hipGetLastError() == hipSuccess ? EOFA_OK : EOFA_ERR_HIP;
 }
 
+// the roles that the library launches in each precision
 template <int P>
 int launch_small_p(int role, const HopArgs& a, hipStream_t st) {
+#define EOFA_CASE(X) \
+  case X: return launch_small_t<P, X>(a, st);
   switch (role) {
-#define EOFA_CASE(X) case X: return launch_small_t<P, X>(a, st);
     EOFA_CASE(ROLE_DSLASH)
     EOFA_CASE(ROLE_DSLASH_DAG)
-    EOFA_CASE(ROLE_K1)
-    EOFA_CASE(ROLE_K2)
+    EOFA_CASE(ROLE_K1T)
+    EOFA_CASE(ROLE_K2T)
     EOFA_CASE(ROLE_K3)
     EOFA_CASE(ROLE_K4)
     EOFA_CASE(ROLE_K4S)
-    EOFA_CASE(ROLE_SRC)
-    EOFA_CASE(ROLE_RES)
-    EOFA_CASE(ROLE_FULLRES)
     EOFA_CASE(ROLE_D1)
     EOFA_CASE(ROLE_D2)
     EOFA_CASE(ROLE_D3)
     EOFA_CASE(ROLE_D4)
     EOFA_CASE(ROLE_D4S)
-    EOFA_CASE(ROLE_DSRC)
-    EOFA_CASE(ROLE_DRES)
-    EOFA_CASE(ROLE_DFULLRES)
-    EOFA_CASE(ROLE_K1T)
-    EOFA_CASE(ROLE_K2T)
-#undef EOFA_CASE
   }
+  if constexpr (P != P16) switch (role) {  // the operator on a plain field
+      EOFA_CASE(ROLE_K1)
+      EOFA_CASE(ROLE_K2)
+    }
+  if constexpr (P == P64) switch (role) {  // sources and true residuals
+      EOFA_CASE(ROLE_SRC)
+      EOFA_CASE(ROLE_RES)
+      EOFA_CASE(ROLE_FULLRES)
+      EOFA_CASE(ROLE_DSRC)
+      EOFA_CASE(ROLE_DRES)
+      EOFA_CASE(ROLE_DFULLRES)
+    }
+#undef EOFA_CASE
   return EOFA_ERR_INVALID;
 }
 
