@@ -37,10 +37,10 @@ __device__ __forceinline__ size_t lex_of(const int L[4], const int x[4]) {
 // alone: half a spinor, half the 36 accumulators). Per s the tile's a and b and
 // those of the neighbours outside the tile go through LDS once, read by
 // neighbouring lanes (16 bytes each of a 192-byte spinor), while the previous s
-// is computed. 16^3 x 32 x 16: 378 us (2.5 TB/s of the compulsory bytes; with
-// the tiles in plain order 412), 24^3 x 32 x 12 898 us. One thread per site and
+// is computed. 16^3 x 32 x 16: 315 us (3.0 TB/s of the compulsory bytes; with the
+// tiles in plain order 369), 24^3 x 32 x 12 864 us (1028). One thread per site and
 // direction, reading its four spinors per s from memory 192 bytes a lane, took
-// 1256 and 3439 us.
+// 1243 and 3408 us.
 constexpr int DV_T = 32;                  // sites per work-group
 constexpr int DV_SLOTS = 5 * DV_T;        // the tile, then DV_T neighbours per direction
 constexpr int DV_ELEMS = DV_SLOTS * 12;   // complex numbers of one field staged per s

@@ -167,9 +167,9 @@ static __device__ void finalize_step(int mode, double sum, const CgState& S, int
   }
 }
 
-// A CG step fused into a hop launch (work-group 0 of each right-hand-side
-// block): the previous launch's nblk partial sums of right-hand side r,
-// reduced by the whole work-group in a fixed order (8 independent sums per
+// A CG step fused into a hop launch, run by one work-group (which one: see HopArgs):
+// the previous launch's nblk partial sums of right-hand side r, reduced by the
+// whole work-group in a fixed order (8 independent sums per
 // thread, then lanes, then waves), then finalize_step on thread 0. red: one
 // double per wave.
 __device__ __forceinline__ void fin_block(int mode, const double* __restrict__ pr, int nblk, const CgState& S, int r,

@@ -124,10 +124,11 @@ struct HopArgs {
   int W;              // waves per work-group (1, 2 or 4)
   int shaped;         // 1: W and rhs_block were asked for: the general form at any size
   int nt_out;         // 1: non-temporal output stores (set by the launcher)
-  // optional CG step fused into a K3 (or D3) launch: work-group 0 of each RHS block
-  // reduces fin_partial [nrhs][fin_nblk] (the previous launch's partial
-  // sums) and applies finalize mode fin_mode to fin_S; null = none (other
-  // roles ignore it)
+  // optional CG step fused into a launch: the partial sums fin_partial [nrhs][fin_nblk]
+  // of the previous launch, reduced, and finalize mode fin_mode on fin_S; null =
+  // none. The general form takes it in K3 / D3, in work-group 0 of each right-hand-side
+  // block; the small form in K1T / D1 and K3 / D3, in a work-group beside the tiles;
+  // launches of other roles are refused with one
   const double* fin_partial;
   int fin_nblk, fin_mode;
   CgState fin_S;

@@ -1410,7 +1410,12 @@ int launch_hop_p(int role, const HopArgs& a, hipStream_t st, int* nb) {
 }
 
 int launch_hop(int prec, int role, const HopArgs& a, hipStream_t st, int* nblk_out) {
-  if (hop_is_small(prec, role, a)) {
+  const bool small = hop_is_small(prec, role, a);
+  // a fused CG step that the launch would leave undone
+  if (a.fin_partial != nullptr && role != ROLE_K3 && role != ROLE_D3 &&
+      !(small && (role == ROLE_K1T || role == ROLE_D1)))
+    return EOFA_ERR_INVALID;
+  if (small) {
     if (nblk_out) *nblk_out = hop_blocks(a.Vh, a.Ls, 1);
     return launch_hop_small(prec, role, a, st);
   }

@@ -236,15 +236,15 @@ __global__ void __launch_bounds__(256) pt_layer_kernel(NetLayerArgs a) {
 // row of its products), and the matrix cores take a part below 2^-126 as zero, so that
 // activations below 2^-102 lose digits. A lane whose sums hold a NaN or lie below
 // MF_TINY (2^12 above that line) does its outputs over as plain FP32 products (mf_plain).
-// What bounds it: vector instructions (5600 per wave and tile of 16 5D sites:
-// transports 288 and splits 264 of each pass), busy about two thirds of the
-// time, then the matrix cores (15 %). Taking two channels of all directions per
-// pass instead of one direction of all channels keeps the columns the XCD's
-// tiles gather at one time within its 4 MB L2 (with 8 channels at once 69 % of
-// the L2 requests missed, 6.4 GB a launch): 8 -> 8 channels, 16^3 x 32 x 16,
-// 1169 -> 985 us, with the outputs streamed past the MALL 948 us (and 2.5 % for
-// the accuracy of the sums); one thread per site, two outputs at a time, took
-// 4067 us.
+// What bounds it: vector instructions (6000 per wave and tile of 16 5D sites at 8 -> 8
+// channels: transports 288 and splits 264 of each pass), busy four fifths of the
+// time, and the 5.3 GB a launch that miss the L2 (5.5 TB/s); the matrix cores are busy
+// 17 %. Taking two channels of all directions per pass instead of one direction of
+// all channels keeps the columns the XCD's tiles gather at one time within its 4 MB
+// L2 (with 8 channels at once 69 % of the L2 requests missed, 6.4 GB a launch): 8 -> 8
+// channels, 16^3 x 32 x 16, 1169 -> 985 us, with the outputs streamed past the MALL
+// 948 us (and 2.5 % for the accuracy of the sums); one thread per site, two outputs
+// at a time, took 4067 us.
 typedef __bf16 b8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned w4_t __attribute__((ext_vector_type(4)));
@@ -545,7 +545,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))
 // one parity and one of two sets of terms: set 0 the transports of mu = 0, 1 with
 // the same-site terms, set 1 those of mu = 2, 3 with the s shifts. A thread loads its
 // site's G_c once for all terms of the set and each transported input once for
-// all its output channels: the loads (G, then the gathers) bound it, 1.5 KB a
+// all its output channels: the loads (G, then the gathers) bound it, 1.7 KB a
 // site for 1 -> 4 channels, where a work-group per term pair and two output
 // channels read 5.8 KB. Sites run in the traversal order, a contiguous eighth
 // per XCD, so that neighbours meet in its L2. 16^3 x 32, Ls = 16: 1 -> 4 channels
